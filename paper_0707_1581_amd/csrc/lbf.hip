@@ -92,6 +92,7 @@ LatDesc make_desc_m(const lb_params& p, uint64_t base) {
   L.key0 = (uint32_t)p.seed;
   L.key1 = (uint32_t)(p.seed >> 32);
   L.thermal = p.kT > 0.0 ? 1u : 0u;
+  L.kinetic = p.gamma_odd != 0.0 || p.gamma_even != 0.0 ? 1u : 0u;
   L.rho0 = (float)p.rho0;
   const double mu = 3.0 * p.kT;  // kT / c_s^2 in lattice units
   constexpr int K0 = M::D + 1;

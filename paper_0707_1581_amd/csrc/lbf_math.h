@@ -49,7 +49,7 @@ struct D3Q19 {
   // mode class: 0 conserved, 1 bulk, 2 shear, 3 odd kinetic, 4 even kinetic
   static constexpr int CLS[Q] = {0, 0, 0, 0, 1, 2, 2, 2, 2, 2, 3, 3, 3, 3, 3, 3, 4, 4, 4};
 
-  template <class F> static LBF_HD void forward(const F d[Q], F mu[Q]);
+  template <bool KIN = true, class F> static LBF_HD void forward(const F d[Q], F mu[Q]);
   template <class F> static LBF_HD void back(const F nu[Q], F d[Q]);
   // equilibrium stress modes in units of rho0/36:
   // mu_4 = |j|^2 / R, mu_5 = (2 jx^2 - jy^2 - jz^2) / R, mu_6 = (jy^2 - jz^2) / R,
@@ -66,8 +66,9 @@ struct D3Q19 {
   }
 };
 
-// mu_k = sum_i 36 a_i e_ki d_i for all 19 modes.
-template <class F>
+// mu_k = sum_i 36 a_i e_ki d_i for all 19 modes; with KIN = false the kinetic
+// modes 10..18 are left out.
+template <bool KIN, class F>
 LBF_HD void D3Q19::forward(const F d[Q], F mu[Q]) {
   // pair sums and differences: X, Y, Z axes; A=(1,1,0) B=(1,-1,0)
   // C=(1,0,1) D=(1,0,-1) E=(0,1,1) F=(0,1,-1) diagonals
@@ -92,11 +93,8 @@ LBF_HD void D3Q19::forward(const F d[Q], F mu[Q]) {
   const F b5 = Pxy - F(2) * Syz;              // shared by k = 5 and 17
   mu[0] = r12 + F(2) * Sax + Sd;              // 1
   mu[4] = Sd - r12;                           // c^2 - 1
-  mu[16] = (r12 + Sd) - F(4) * Sax;           // 3c^4 - 6c^2 + 1
   mu[5] = (b5 - F(2) * Tyz) + F(4) * sX;      // 3cx^2 - c^2
-  mu[17] = (b5 + F(2) * Tyz) - F(4) * sX;     // (2c^2-3)(3cx^2-c^2)
   mu[6] = F(2) * Dyz + Mxy;                   // cy^2 - cz^2
-  mu[18] = Mxy - F(2) * Dyz;                  // (2c^2-3)(cy^2-cz^2)
   mu[7] = sA - sB;                            // cx cy
   mu[8] = sE - sF;                            // cy cz
   mu[9] = sC - sD;                            // cz cx
@@ -108,12 +106,17 @@ LBF_HD void D3Q19::forward(const F d[Q], F mu[Q]) {
   mu[1] = F(2) * dX + Ux;                     // cx
   mu[2] = F(2) * dY + Uy;                     // cy
   mu[3] = F(2) * dZ + Uz;                     // cz
-  mu[10] = Ux - F(4) * dX;                    // (3c^2-5) cx
-  mu[11] = Uy - F(4) * dY;                    // (3c^2-5) cy
-  mu[12] = Uz - F(4) * dZ;                    // (3c^2-5) cz
-  mu[13] = (dA + dB) - (dC + dD);             // (cy^2-cz^2) cx
-  mu[14] = (dE + dF) - (dA - dB);             // (cz^2-cx^2) cy
-  mu[15] = (dC - dD) - (dE - dF);             // (cx^2-cy^2) cz
+  if constexpr (KIN) {
+    mu[16] = (r12 + Sd) - F(4) * Sax;           // 3c^4 - 6c^2 + 1
+    mu[17] = (b5 + F(2) * Tyz) - F(4) * sX;     // (2c^2-3)(3cx^2-c^2)
+    mu[18] = Mxy - F(2) * Dyz;                  // (2c^2-3)(cy^2-cz^2)
+    mu[10] = Ux - F(4) * dX;                    // (3c^2-5) cx
+    mu[11] = Uy - F(4) * dY;                    // (3c^2-5) cy
+    mu[12] = Uz - F(4) * dZ;                    // (3c^2-5) cz
+    mu[13] = (dA + dB) - (dC + dD);             // (cy^2-cz^2) cx
+    mu[14] = (dE + dF) - (dA - dB);             // (cz^2-cx^2) cy
+    mu[15] = (dC - dD) - (dE - dF);             // (cx^2-cy^2) cz
+  }
 }
 
 // d_i = sum_k e_ki nu_k for all 19 populations.
@@ -177,7 +180,7 @@ struct D2Q9 {
 
   // mu_k = sum_i 36 a_i e_ki d_i.  Pairs: X = (1, 2), Y = (3, 4),
   // A = (1,1) (5, 6), B = (1,-1) (7, 8).
-  template <class F> static LBF_HD void forward(const F d[Q], F mu[Q]) {
+  template <bool KIN = true, class F> static LBF_HD void forward(const F d[Q], F mu[Q]) {
     const F sX = d[1] + d[2], dX = d[1] - d[2];
     const F sY = d[3] + d[4], dY = d[3] - d[4];
     const F sA = d[5] + d[6], dA = d[5] - d[6];
@@ -188,12 +191,14 @@ struct D2Q9 {
     mu[3] = F(4) * (Sax + Sd) - F(2) * r16;                   // 3c^2 - 2
     mu[4] = F(4) * (sX - sY);                                 // 2cx^2 - c^2
     mu[5] = sA - sB;                                          // cx cy
-    mu[8] = (F(2) * r16 - F(16) * Sax) + F(8) * Sd;           // 9c^4 - 15c^2 + 2
     const F Px = dA + dB, Py = dA - dB;
     mu[1] = F(4) * dX + Px;                                   // cx
     mu[2] = F(4) * dY + Py;                                   // cy
-    mu[6] = F(2) * Px - F(4) * dX;                            // (3c^2 - 4) cx
-    mu[7] = F(2) * Py - F(4) * dY;                            // (3c^2 - 4) cy
+    if constexpr (KIN) {
+      mu[6] = F(2) * Px - F(4) * dX;                          // (3c^2 - 4) cx
+      mu[7] = F(2) * Py - F(4) * dY;                          // (3c^2 - 4) cy
+      mu[8] = (F(2) * r16 - F(16) * Sax) + F(8) * Sd;         // 9c^4 - 15c^2 + 2
+    }
   }
 
   // d_i = sum_k e_ki nu_k.
