@@ -685,11 +685,46 @@ int init_lattice(lb_ctx* c, int idx, int kind, const float* d_fields, int parity
   return LB_OK;
 }
 
-// Default schedule, from measurements on MI355X (512^3 D3Q19 and 16384^2
-// D2Q9 boxes): fp32 runs the even step row-tiled and the odd step flat, both
-// without XCD remapping; the 16-bit forms run the even step flat and the odd
-// step row-tiled, with XCD groups of 8 consecutive tiles on D3Q19 and no
-// remapping on D2Q9 (groups of 8 made the D2Q9 bf16 step 10% slower).
+// Launch shape of the AA steps: block size, tilings and XCD remap, from
+// measurements on MI355X.
+// One lattice of more than 320 MB streams through HBM in long rows: fp32 runs
+// the even step row-tiled and the odd step flat, both without XCD remapping;
+// the 16-bit forms run the even step flat and the odd step row-tiled, with
+// XCD groups of 8 consecutive tiles on D3Q19 and no remapping on D2Q9 (groups
+// of 8 made the D2Q9 bf16 step 10% slower).  So do smaller 16-bit lattices
+// whose rows fill the row tiles (256 x 256 x 24 fp16: 23.0 us per step, flat
+// 24.3; 4096^2 bf16 114 against 118), D2Q9 with groups of 8 up to 128 MB (1024^2
+// bf16 10.6 against 12.0 us).
+// Other smaller lattices and batches run flat: their rows are seldom a multiple of
+// a row tile's 256 lanes, and the idle lanes cost more than the per-lane
+// division the flat tiling adds (96-replica fp16 ensemble 501 against 405 us
+// per step, fp32 748 against 711; 128^3 fp16 36.9 against 28.5; 64^3 fp32
+// 11.6 against 7.5; 97 x 131 x 75 bf16 19.1 against 17.3; 1000^2 fp32 19.2
+// against 13.6), with XCD groups of 8 so that neighbouring tiles share an L2.
+// The smallest take smaller workgroups, so that more CUs work on them (16^3
+// fp32 4.3 us with 256 lanes, 3.9 with 64; 32^3 4.5 and 4.3 with 128).
+struct AaShape {
+  int block;
+  int remap[2];
+  int tiling[2];
+};
+AaShape aa_shape(const lb_params* reps, size_t nrep) {
+  uint64_t sites = 0, bytes = 0;
+  for (size_t r = 0; r < nrep; ++r) {
+    sites += sites_of(reps[r]);
+    bytes += (uint64_t)q_of(reps[r].lattice) * sites_of(reps[r]) * elem_size(reps[r].storage);
+  }
+  const bool full_rows = nrep == 1 && reps[0].nx % 256 == 0 && reps[0].storage != LB_F32;
+  if (nrep > 1 || (bytes <= 320000000ull && !full_rows))
+    return {sites <= 16384 ? 64 : sites <= 65536 ? 128 : 256, {8, 8}, {0, 0}};
+  AaShape s{256, {0, 0}, {0, 0}};
+  if (bytes <= 128000000ull) s.remap[0] = s.remap[1] = 8;
+  if (reps[0].storage != LB_F32 && reps[0].lattice == LB_D3Q19) s.remap[0] = s.remap[1] = 8;
+  if (!is_wide(reps[0])) s.tiling[reps[0].storage == LB_F32 ? 0 : 1] = 1;
+  return s;
+}
+
+// Default schedule: the launch shape above, and from measurements on MI355X:
 // State of 32 MB to 320 MB on one lattice runs resident in the Infinity
 // Cache (4-14% faster from 96^3 to 160^3), unless fp32 state above 256 MiB
 // (D2Q9: 32 MiB) takes the fused pass (below); a batch whose replicas each
@@ -698,10 +733,8 @@ int init_lattice(lb_ctx* c, int idx, int kind, const float* d_fields, int parity
 // policy measured as fast or faster.  lb_autotune refines it for a given
 // workload.
 int default_schedule(lb_ctx* c) {
-  if (c->storage == LB_F32) c->sched = lb_schedule{256, 0, 16, {0, 0}, {1, 0}, 0, 0, 0};
-  else if (c->lattice == LB_D2Q9) c->sched = lb_schedule{256, 0, 16, {0, 0}, {0, 1}, 0, 0, 0};
-  else c->sched = lb_schedule{256, 0, 16, {8, 8}, {0, 1}, 0, 0, 0};
-  if (c->wide) c->sched.tiling[0] = c->sched.tiling[1] = 0;
+  const AaShape sh = aa_shape(c->reps.data(), c->reps.size());
+  c->sched = lb_schedule{sh.block, 0, 16, {sh.remap[0], sh.remap[1]}, {sh.tiling[0], sh.tiling[1]}, 0, 0, 0};
   uint64_t total = 0, largest = 0;
   for (const lb_params& p : c->reps) {
     const uint64_t b = (uint64_t)q_of(p.lattice) * sites_of(p) * elem_size(p.storage);
@@ -1504,16 +1537,10 @@ int lb_step_noalloc(const lb_params* reps, int32_t nrep, void* d_pool, void* hip
   hipStream_t st = (hipStream_t)hip_stream;
 
   // the library's default launch shape, streaming cache policy, one launch per step
-  constexpr int BLOCK = 256;
+  const AaShape shape = aa_shape(reps, (size_t)nrep);
+  const uint32_t BLOCK = (uint32_t)shape.block;
   const int storage = reps[0].storage, lattice = reps[0].lattice;
   const bool wide = is_wide(reps[0]);
-  int tiling[2] = {1, 0}, remap[2] = {0, 0};
-  if (storage != LB_F32) {
-    tiling[0] = 0;
-    tiling[1] = 1;
-    if (lattice == LB_D3Q19) remap[0] = remap[1] = 8;
-  }
-  if (wide) tiling[0] = tiling[1] = 0;
 
   // descriptors, in chunks passed by value, then the tile prefixes and the step counter
   NaMeta meta{};
@@ -1550,12 +1577,12 @@ int lb_step_noalloc(const lb_params* reps, int32_t nrep, void* d_pool, void* hip
     const int64_t m = std::min<int64_t>(16, nsteps - s0);
     for (int64_t s = 0; s < m; ++s) {
       const int parity = (int)((t0 + s0 + s) & 1);
-      const bool rows = tiling[parity] != 0;
-      void* fn = rows ? rows_ptr(lattice, storage, parity, false, BLOCK, false)
-                      : step_ptr(lattice, storage, parity, wide, false, BLOCK, false);
+      const bool rows = shape.tiling[parity] != 0;
+      void* fn = rows ? rows_ptr(lattice, storage, parity, false, (int)BLOCK, false)
+                      : step_ptr(lattice, storage, parity, wide, false, (int)BLOCK, false);
       const LatDesc* lats = d_lats;
       const uint32_t* blk = rows ? d_blk_rows : d_blk;
-      uint32_t rm = (uint32_t)remap[parity];
+      uint32_t rm = (uint32_t)shape.remap[parity];
       const uint64_t* dt = d_t;
       uint32_t t_off = (uint32_t)s;
       uint32_t nl = nlat;
