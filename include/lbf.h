@@ -135,10 +135,11 @@ size_t lb_state_bytes(const lb_params* p);
  * (t0 >= 0); d_fields is required for LB_INIT_FIELDS and ignored otherwise.
  * The context stores p by value.  Its default schedule (lb_get_schedule)
  * depends on the state: an fp32 lattice of more than 256 MiB (D3Q19) or
- * 32 MiB (D2Q9) takes the fused two-step schedule when the device has room
- * for its second state buffer (and its z-planes, or D2Q9 rows, hold less
- * than 4 GiB per population), which lb_init then allocates (release it with
- * lb_set_schedule and fused = 0).  With LB_BF16 storage and kT = 0
+ * 32 MiB (D2Q9), or a 16-bit D2Q9 one of more than 320 MB, takes the fused
+ * schedule when the device has room for its second state buffer (16 bits:
+ * when that is at most a quarter of the free memory) and its z-planes, or
+ * D2Q9 rows, hold less than 4 GiB per population; lb_init then allocates the
+ * buffer (release it with lb_set_schedule and fused = 0).  With LB_BF16 storage and kT = 0
  * it succeeds and leaves a warning in lb_last_error(). */
 int lb_init(const lb_params* p, void* d_state, void* hip_stream, int32_t init_kind,
             const float* d_fields, int64_t t0, lb_ctx** out);
@@ -146,7 +147,8 @@ int lb_init(const lb_params* p, void* d_state, void* hip_stream, int32_t init_ki
 /* Enqueue nsteps >= 0 steps (collide with noise keyed on the current t,
  * then push).  Full chunks of steps are replayed from a HIP graph (launched
  * one by one instead when a replay would exceed 2^16 kernel launches:
- * graph_chunk times the number of replica groups). */
+ * graph_chunk times the number of replica groups; and under the fused
+ * schedule on a lattice of 64 MB or more). */
 int lb_step(lb_ctx* ctx, int64_t nsteps);
 
 /* Enqueue nsteps >= 0 propagation-only steps: the streaming half of
@@ -260,10 +262,11 @@ typedef struct {
                         /* group, and a graph replay runs all graph_chunk      */
                         /* steps of one group before the next.  Replicas are   */
                         /* independent, so results do not depend on it.        */
-  int32_t fused;        /* 0: one in-place AA launch per step.  1: two steps   */
-                        /* per launch: from even t, each launch reads the      */
-                        /* state once and writes the state two steps later     */
-                        /* into a second buffer that the library allocates     */
+  int32_t fused;        /* 0: one in-place AA launch per step.  1: several     */
+                        /* steps per launch (D3Q19 two, D2Q9 two to four):     */
+                        /* from even t, each launch reads the state once and   */
+                        /* writes the state those steps later into a second    */
+                        /* buffer that the library allocates                   */
                         /* (the size of the state) and releases when the       */
                         /* schedule goes back to 0 or the context is           */
                         /* destroyed.  Pairs of launches return the state to   */
@@ -293,7 +296,7 @@ int lb_set_schedule(lb_ctx* ctx, const lb_schedule* s);
  * interleaved rounds) with each cache policy and, for a batch, replica
  * groups of 0, 64, 128, 160, 192, 224 and 256 MiB, and keeps a variant
  * only if it is at least 1% faster than the first stage's choice; a single
- * lattice also tries the fused two-step schedule there (when the
+ * lattice also tries the fused schedule there (when the
  * device has room for its second buffer).  Applies the best schedule and
  * writes a JSON report (one object per first-stage candidate with its mean
  * even and odd step times, plus refined_even_ms / refined_odd_ms for the

@@ -15,7 +15,7 @@
 
 #include "lbf.h"
 #include "lbf_kernels.h"
-#include "lbf_fused2d.h"
+#include "lbf_strip2d.h"
 
 using namespace lbf;
 
@@ -201,25 +201,26 @@ void* rows_ptr(int lattice, int storage, int parity, bool res, int block, bool p
                             : rows_ptr_m<D3Q19, false>(storage, parity, res, block);
 }
 
-// Fused two-step passes (D3Q19 and D2Q9): step kernels and their
-// propagation-only twins; wide: planes of 4 GiB or more, addressed one
-// z-plane (row) at a time.
-template <int S, bool W>
-void* step2_ptr_s(int lattice, bool prop) {
-  if (lattice == LB_D2Q9) return prop ? (void*)&k_step2_2d<S, true, W> : (void*)&k_step2_2d<S, false, W>;
-  return prop ? (void*)&k_step2<S, true, W> : (void*)&k_step2<S, false, W>;
+// Fused passes of k steps per launch (D3Q19: k = 2, wide: planes of 4 GiB or
+// more, addressed one z-plane at a time; D2Q9: k = 2, 3 or 4) and their
+// propagation-only twins.
+template <int S>
+void* pass_ptr_s(int lattice, int k, bool wide, bool prop) {
+  if (lattice == LB_D2Q9) {
+    if (k == 4) return prop ? (void*)&k_strip2d<S, true, 4> : (void*)&k_strip2d<S, false, 4>;
+    if (k == 3) return prop ? (void*)&k_strip2d<S, true, 3> : (void*)&k_strip2d<S, false, 3>;
+    return prop ? (void*)&k_strip2d<S, true, 2> : (void*)&k_strip2d<S, false, 2>;
+  }
+  if (wide) return prop ? (void*)&k_step2<S, true, true> : (void*)&k_step2<S, false, true>;
+  return prop ? (void*)&k_step2<S, true, false> : (void*)&k_step2<S, false, false>;
 }
-template <bool W>
-void* step2_ptr_w(int lattice, int storage, bool prop) {
+void* pass_ptr(int lattice, int storage, int k, bool wide, bool prop) {
   switch (storage) {
-    case LB_F32: return step2_ptr_s<ST_F32, W>(lattice, prop);
-    case LB_F16: return step2_ptr_s<ST_F16, W>(lattice, prop);
-    case LB_BF16: return step2_ptr_s<ST_BF16, W>(lattice, prop);
+    case LB_F32: return pass_ptr_s<ST_F32>(lattice, k, wide, prop);
+    case LB_F16: return pass_ptr_s<ST_F16>(lattice, k, wide, prop);
+    case LB_BF16: return pass_ptr_s<ST_BF16>(lattice, k, wide, prop);
   }
   return nullptr;
-}
-void* step2_ptr(int lattice, int storage, bool wide, bool prop) {
-  return wide ? step2_ptr_w<true>(lattice, storage, prop) : step2_ptr_w<false>(lattice, storage, prop);
 }
 
 // Initial states (rest, thermal, fields), gathers (populations, moments,
@@ -318,20 +319,32 @@ struct lb_ctx {
   } adv_args;
 
   // fused schedule: the second state buffer (library-owned), the descriptors
-  // of both buffers (d_f2[0] the state, d_f2[1] the second buffer), the tile
-  // grid of k_step2 (D3Q19) or k_step2_2d (D2Q9), the planes (rows) a tile
-  // walks and the workgroup size
+  // of both buffers (d_f2[0] the state, d_f2[1] the second buffer), the
+  // launches of its passes and the most steps a pass takes
   char* d_state_b = nullptr;
   LatDesc* d_f2 = nullptr;
-  uint32_t f2_ntx = 0, f2_nty = 0, f2_ntz = 0, f2_len = 0;
-  int f2_threads = 0;
-  struct F2Args {
+  struct PassPlan {
+    uint32_t ntx = 0, nty = 0, len = 0;  // D3Q19 tiles
+    StripGeom strip{};                   // D2Q9 strips
+    uint32_t grid = 0;
+    int threads = 0;
+  };
+  PassPlan plans[3];  // passes of 2, 3 and 4 steps
+  int pass_max = 2;
+  struct PassArgs {
     const LatDesc* src;
     uint64_t dst;
+    PassSide from, to;
     const uint64_t* d_t;
     uint32_t t_off, ntx, nty, zlen;
+    StripGeom strip;
+    // the kernel's arguments in order
+    std::vector<void*> list(int lattice) {
+      if (lattice == LB_D2Q9) return {&src, &from, &to, &d_t, &t_off, &strip};
+      return {&src, &dst, &d_t, &t_off, &ntx, &nty, &zlen};
+    }
   };
-  std::vector<F2Args> graph_f2_args;
+  std::vector<PassArgs> graph_pass_args;
 
   lb_ctx* root() { return parent ? parent : this; }
 };
@@ -345,12 +358,12 @@ void drop_graph(lb_ctx* c) {
   c->graph = nullptr;
 }
 
-// Planes (D3Q19: z-planes; D2Q9: rows) per tile column of the fused pass,
+// Planes per tile column of the D3Q19 fused pass,
 // for `across` tiles per plane, `extent` planes and `slots` tiles resident
 // on the device at a time (CUs times tiles per CU).  A pass runs in rounds
 // of `slots` tiles, each round taking one tile's chunk + 3 phases plus about
 // one of set-up.  Lattices with many rounds take 32 planes (the fastest at
-// 512^3 and 16384^2); with few, a last round that leaves many CUs idle costs
+// 512^3); with few, a last round that leaves many CUs idle costs
 // a large part of the pass, and the chunk length from 8 to 32 that
 // minimises the estimate is taken instead (256^3 on 256 CUs: 22 planes, 5
 // rounds of 26 phases instead of 4 of 36).  The result does not depend on it.
@@ -363,6 +376,51 @@ uint32_t fused_chunk(uint64_t across, uint32_t extent, uint32_t slots) {
   for (uint32_t z = 8; z < LONG; ++z)
     if (cost(z) < cost(best)) best = z;
   return best;
+}
+
+// Rows a strip of the D2Q9 pass walks: as many strips as the device holds
+// waves at a time (slots), up to 64 rows (16384^2 fp32: 1.59 ms per step with
+// 32 rows, 1.57 with 64, 1.59 with 128, 1.62 with 256); shorter strips repeat
+// their halo rows more often than the waves they add are worth (2048^2 fp32:
+// 43.9 us per step with 4 rows, 34.0 with 16, 57.7 with 64).
+uint32_t strip_rows(uint32_t across, uint32_t extent, uint32_t slots) {
+  const uint64_t rows = ((uint64_t)across * extent + slots - 1u) / slots;
+  return (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, rows));
+}
+
+// Tiles of the passes over the lattice of c (CUs: the device's).
+int plan_passes(lb_ctx* c) {
+  const LatDesc& L = c->lats[0];
+  int cus = 0;
+  HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
+  c->pass_max = 2;
+  for (int k = 2; k <= (c->lattice == LB_D2Q9 ? 4 : 2); ++k) {
+    lb_ctx::PassPlan& p = c->plans[k - 2];
+    p.threads = c->lattice == LB_D2Q9 ? 64 * S2_WAVES : F2_THREADS;
+    int per_cu = 0;
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pass_ptr(c->lattice, c->storage, k, c->wide, false),
+                                                         p.threads, 0));
+    const uint32_t slots = (uint32_t)std::max(1, cus * per_cu);  // workgroups resident at a time
+    if (c->lattice == LB_D2Q9) {
+      StripGeom& g = p.strip;
+      const uint32_t w = 64u - 2u * (uint32_t)(k - 1);
+      g.ntx = (L.nx + w - 1u) / w;
+      g.tx = (L.nx + g.ntx - 1u) / g.ntx;
+      g.len = strip_rows(g.ntx, L.ny, slots * S2_WAVES);
+      g.nty = (L.ny + g.len - 1u) / g.len;
+      p.grid = (g.ntx * g.nty + S2_WAVES - 1u) / S2_WAVES;
+      // Strips of few rows spend more on the wider halo of four steps than
+      // they save (1024^2 fp32, 4 rows: 14.2 us per step, with two 12.9;
+      // 2048^2, 15 rows: 34.0 and 37.9).
+      if (k == 4 && g.len >= 8) c->pass_max = 4;
+    } else {
+      p.ntx = (L.nx + 63u) / 64u;
+      p.nty = (L.ny + (uint32_t)F2_TY - 1u) / (uint32_t)F2_TY;
+      p.len = fused_chunk((uint64_t)p.ntx * p.nty, L.nz, slots);
+      p.grid = p.ntx * p.nty * ((L.nz + p.len - 1u) / p.len);
+    }
+  }
+  return LB_OK;
 }
 
 // Tile order, replica groups and the per-lattice block prefixes (relative to
@@ -417,24 +475,8 @@ int upload_schedule(lb_ctx* c) {
     LatDesc f2[2] = {c->lats[0], c->lats[0]};
     f2[1].base = (uint64_t)(uintptr_t)c->d_state_b;
     HIP_TRY(hipMemcpy(c->d_f2, f2, sizeof(f2), hipMemcpyHostToDevice));
-    const bool d2 = c->lattice == LB_D2Q9;
-    c->f2_threads = d2 ? F2D_THREADS : F2_THREADS;
-    int cus = 0, per_cu = 0;
-    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, step2_ptr(c->lattice, c->storage, c->wide, false),
-                                                         c->f2_threads, 0));
-    const uint32_t slots = (uint32_t)std::max(1, cus * per_cu);
-    if (d2) {
-      c->f2_ntx = (f2[0].nx + (uint32_t)F2D_W - 1u) / (uint32_t)F2D_W;
-      c->f2_len = fused_chunk(c->f2_ntx, f2[0].ny, slots);
-      c->f2_nty = (f2[0].ny + c->f2_len - 1u) / c->f2_len;
-      c->f2_ntz = 1;
-    } else {
-      c->f2_ntx = (f2[0].nx + 63u) / 64u;
-      c->f2_nty = (f2[0].ny + (uint32_t)F2_TY - 1u) / (uint32_t)F2_TY;
-      c->f2_len = fused_chunk((uint64_t)c->f2_ntx * c->f2_nty, f2[0].nz, slots);
-      c->f2_ntz = (f2[0].nz + c->f2_len - 1u) / c->f2_len;
-    }
+    const int rc = plan_passes(c);
+    if (rc) return rc;
   }
   drop_graph(c);
   return LB_OK;
@@ -509,19 +551,53 @@ int launch_step(lb_ctx* c, uint32_t t_off, int parity, bool prop = false) {
   return LB_OK;
 }
 
-// One fused pass (two steps from even t + t_off): state buffer -> second
-// buffer (to_b) or back.
-lb_ctx::F2Args pass_args(const lb_ctx* c, uint32_t t_off, bool to_b) {
-  return {to_b ? c->d_f2 : c->d_f2 + 1,
-          to_b ? (uint64_t)(uintptr_t)c->d_state_b : c->lats[0].base,
-          c->d_t, t_off, c->f2_ntx, c->f2_nty, c->f2_len};
+// Steps of the passes that cover the first of m steps from even t: an even
+// number of passes (out to the second buffer and back) over an even number of
+// steps (the layout they leave is that of an even t); the rest, fewer than
+// four steps, runs as AA steps.  Where passes of four steps pay, as few passes
+// as cover the steps, of sizes as equal as they can be: a pass of two moves as
+// many bytes as one of four (16384^2 fp32: passes of 2, 3 and 4 steps take 5.5,
+// 4.9 and 6.3 ms), so 20 steps are 4 + 4 + 3 + 3 + 3 + 3.
+std::vector<int> pass_steps(const lb_ctx* c, int64_t m) {
+  const int64_t most = c->pass_max;
+  int64_t left = m & ~(int64_t)1, passes = 2 * (left / (2 * most));
+  if (left - most * passes >= 4) passes += 2;
+  else left = most * passes;
+  std::vector<int> ks((size_t)passes);
+  for (int64_t p = 0; p < passes; ++p) {
+    const int64_t n = (left + (passes - p) - 1) / (passes - p);  // the larger ones first
+    ks[(size_t)p] = (int)n;
+    left -= n;
+  }
+  return ks;
 }
 
-int launch_pass(lb_ctx* c, uint32_t t_off, bool to_b, bool prop = false) {
-  lb_ctx::F2Args a = pass_args(c, t_off, to_b);
-  void* args[] = {&a.src, &a.dst, &a.d_t, &a.t_off, &a.ntx, &a.nty, &a.zlen};
-  HIP_TRY(hipLaunchKernel(step2_ptr(c->lattice, c->storage, c->wide, prop), dim3(c->f2_ntx * c->f2_nty * c->f2_ntz),
-                          dim3(c->f2_threads), args, 0, c->stream));
+// One pass of k steps from even t + t_off: state buffer -> second buffer
+// (to_b) or back.
+lb_ctx::PassArgs pass_args(const lb_ctx* c, uint32_t t_off, bool to_b, int k) {
+  const LatDesc& L = c->lats[0];
+  const lb_ctx::PassPlan& p = c->plans[k - 2];
+  const uint64_t b = (uint64_t)(uintptr_t)c->d_state_b;
+  const uint32_t es = (uint32_t)elem_size(c->storage), row = L.nx * es;
+  const PassSide A{L.base, L.plane * es, row, row};
+  PassSide B = A;
+  B.base = b;
+  // the second D2Q9 buffer holds the nine populations of a row side by side
+  // (see k_strip2d) where such a row fits the range of a buffer descriptor
+  const uint64_t q = (uint64_t)q_of(c->lattice);
+  if (q * row < (1ull << 32)) {
+    B.plane = row;
+    B.slice = B.span = (uint32_t)q * row;
+  }
+  return {to_b || c->lattice == LB_D2Q9 ? c->d_f2 : c->d_f2 + 1, to_b ? b : L.base, to_b ? A : B, to_b ? B : A,
+          c->d_t, t_off, p.ntx, p.nty, p.len, p.strip};
+}
+
+int launch_pass(lb_ctx* c, uint32_t t_off, bool to_b, int k, bool prop = false) {
+  lb_ctx::PassArgs a = pass_args(c, t_off, to_b, k);
+  const lb_ctx::PassPlan& p = c->plans[k - 2];
+  HIP_TRY(hipLaunchKernel(pass_ptr(c->lattice, c->storage, k, c->wide, prop), dim3(p.grid), dim3(p.threads),
+                          a.list(c->lattice).data(), 0, c->stream));
   return LB_OK;
 }
 
@@ -534,15 +610,17 @@ int launch_advance(lb_ctx* c, uint64_t n) {
 // A chain of graph_chunk steps of each group in turn (all steps of one group
 // before the next, so a group whose state fits in the Infinity Cache stays
 // there), then the counter advance.  Under the fused schedule (one lattice)
-// the chain is fused passes, out to the second buffer and back, for every
-// four steps, and AA steps for the rest of the chunk.
+// the chain is pairs of fused passes, out to the second buffer and back, and
+// AA steps for the rest of the chunk.
 int build_graph(lb_ctx* c) {
   drop_graph(c);
   const int K = c->sched.graph_chunk;
-  const int units = c->sched.fused ? K / 4 : 0;  // pairs of fused passes
+  const std::vector<int> ks = c->sched.fused ? pass_steps(c, K) : std::vector<int>();
+  int covered = 0;
+  for (int k : ks) covered += k;
   HIP_TRY(hipGraphCreate(&c->graph, 0));
-  c->graph_args.assign((K - 4 * units) * c->groups.size(), {});
-  c->graph_f2_args.assign(2 * units, {});
+  c->graph_args.assign((K - covered) * c->groups.size(), {});
+  c->graph_pass_args.assign(ks.size(), {});
   hipGraphNode_t prev = nullptr;
   auto add_node = [&](void* fn, uint32_t grid, int block, void** args) -> int {
     hipKernelNodeParams kp{};
@@ -557,18 +635,19 @@ int build_graph(lb_ctx* c) {
     prev = node;
     return LB_OK;
   };
-  for (int p = 0; p < 2 * units; ++p) {
-    c->graph_f2_args[p] = pass_args(c, (uint32_t)(2 * p), (p & 1) == 0);
-    lb_ctx::F2Args& a = c->graph_f2_args[p];
-    void* args[] = {&a.src, &a.dst, &a.d_t, &a.t_off, &a.ntx, &a.nty, &a.zlen};
-    int rc = add_node(step2_ptr(c->lattice, c->storage, c->wide, false), c->f2_ntx * c->f2_nty * c->f2_ntz, c->f2_threads,
-                      args);
+  uint32_t at = 0;
+  for (size_t n = 0; n < ks.size(); ++n) {
+    c->graph_pass_args[n] = pass_args(c, at, (n & 1) == 0, ks[n]);
+    const lb_ctx::PassPlan& p = c->plans[ks[n] - 2];
+    int rc = add_node(pass_ptr(c->lattice, c->storage, ks[n], c->wide, false), p.grid, p.threads,
+                      c->graph_pass_args[n].list(c->lattice).data());
     if (rc) return rc;
+    at += (uint32_t)ks[n];
   }
-  const int K1 = K - 4 * units;  // AA steps per group, from step 4 * units of the chunk
+  const int K1 = K - covered;  // AA steps per group, from step `covered` of the chunk
   for (size_t n = 0; n < c->graph_args.size(); ++n) {
     const size_t g = n / K1;
-    const int s = 4 * units + (int)(n % K1);
+    const int s = covered + (int)(n % K1);
     const StepLaunch sl = step_launch(c, s & 1, g);
     if (!sl.fn) return fail(LB_EINVAL, "no step kernel for this schedule");
     c->graph_args[n] = {sl.lats, sl.blk, sl.nlat, (uint32_t)c->sched.xcd_remap[s & 1], c->d_t, (uint32_t)s};
@@ -586,15 +665,17 @@ int build_graph(lb_ctx* c) {
 }
 
 // m steps launched one by one (prop: the propagation-only kernels), then the
-// counter advance.  Under the fused schedule, from even t, every four steps
-// run as two fused passes (out to the second buffer and back).
+// counter advance.  Under the fused schedule, from even t, pairs of fused
+// passes (out to the second buffer and back) cover all but the last steps.
 int direct_steps(lb_ctx* c, int64_t m, bool prop = false) {
   int64_t s = 0;
   if (c->sched.fused && !(c->t & 1)) {
-    for (; s + 4 <= m; s += 4) {
-      int rc = launch_pass(c, (uint32_t)s, true, prop);
-      if (!rc) rc = launch_pass(c, (uint32_t)s + 2u, false, prop);
+    bool to_b = true;
+    for (int k : pass_steps(c, m)) {
+      int rc = launch_pass(c, (uint32_t)s, to_b, k, prop);
       if (rc) return rc;
+      s += k;
+      to_b = !to_b;
     }
   }
   for (; s < m; ++s) {
@@ -617,8 +698,13 @@ int advance(lb_ctx* c, int64_t n) {
     --n;
   }
   // a replay holds K launches per replica group; past 2^16 kernel nodes the
-  // steps are launched directly instead (same work, more host launches)
-  const bool graphable = (uint64_t)K * c->groups.size() <= (1u << 16);
+  // steps are launched directly instead (same work, more host launches).  So
+  // are the passes of a fused lattice of 64 MB or more (40 us or more apiece):
+  // the host stays ahead of them, and all n steps are divided among the passes
+  // at once (20 steps of 16384^2 fp32: 34.9 ms, as a replay of 16 and 4 more
+  // 38.0).
+  const bool long_passes = c->sched.fused && c->lats[0].plane * q_of(c->lattice) * elem_size(c->storage) >= 64000000;
+  const bool graphable = (uint64_t)K * c->groups.size() <= (1u << 16) && !long_passes;
   if (n >= K && graphable) {
     if (!c->graph_exec) {
       int rc = build_graph(c);
@@ -631,7 +717,7 @@ int advance(lb_ctx* c, int64_t n) {
     }
   }
   while (n > 0) {  // the device counter advances every K steps, as in a replay
-    const int64_t m = std::min<int64_t>(n, K);
+    const int64_t m = std::min<int64_t>(n, long_passes ? 1024 : K);
     int rc = direct_steps(c, m);
     if (rc) return rc;
     n -= m;
@@ -750,19 +836,25 @@ int default_schedule(lb_ctx* c) {
       c->sched.group_mb = 224;
     }
   }
-  // fp32 state beyond the cache streams through HBM: two fused steps per
-  // launch move about half the bytes (512^3 D3Q19: 5.2-5.4 against 7.2 ms
-  // per two steps; 16384^2 D2Q9: 4.35 against 6.84 ms), when the second
-  // buffer fits on the device; planes of 4 GiB or more included.  Measured
-  // crossovers against the resident AA steps: D3Q19 between 152^3 (267 MB,
-  // AA 8% faster) and 156^3 (289 MB, fused 13% faster), D2Q9 between 724^2
-  // (19 MB, AA 6% faster) and 1024^2 (38 MB, fused 11% faster).  The 16-bit
-  // forms keep one step per launch: their collision already keeps the VALU
-  // busy enough that the fused pass is slower.
-  const uint64_t fused_above = c->lattice == LB_D2Q9 ? 32 * MIB : 256 * MIB;
-  if (c->storage == LB_F32 && fused_eligible(c) && total > fused_above) {
+  // State beyond the cache streams through HBM: passes of two (D3Q19) or four
+  // (D2Q9) fused steps per launch move a fraction of the bytes, when the
+  // second buffer fits on the device; planes of 4 GiB or more included.
+  // Measured crossovers of fp32 against the resident AA steps: D3Q19 between
+  // 152^3 (267 MB, AA 8% faster) and 156^3 (289 MB, fused 13% faster), D2Q9
+  // between 724^2 (19 MB, AA 6% faster) and 1024^2 (38 MB, fused 7% faster).
+  // 16-bit D2Q9 state takes them above the resident band (16384^2 bf16: 1.49
+  // against 1.76 ms per step; 4096^2, inside it, 108 against 118 us; 2048^2 36
+  // against 31).  16-bit D3Q19 state keeps one step per launch: its collision
+  // already keeps the VALU busy enough that the fused pass is slower.
+  const bool d2 = c->lattice == LB_D2Q9;
+  const uint64_t fused_above = d2 ? (c->storage == LB_F32 ? 32 * MIB : 320 * MB) : 256 * MIB;
+  if ((d2 || c->storage == LB_F32) && fused_eligible(c) && total > fused_above) {
     const std::string keep = g_last_error;
-    if (ensure_state_b(c) == LB_OK) c->sched.fused = 1;
+    size_t free_b = 0, total_b = 0;
+    // 16-bit state: only where the second buffer is a small part of what is
+    // free, so that large 16-bit lattices keep the memory they are chosen for
+    const bool room = c->storage == LB_F32 || (hipMemGetInfo(&free_b, &total_b) == hipSuccess && 4 * total <= free_b);
+    if (room && ensure_state_b(c) == LB_OK) c->sched.fused = 1;
     else g_last_error = keep;  // no room: one step per launch, not an error
   }
   return upload_schedule(c);

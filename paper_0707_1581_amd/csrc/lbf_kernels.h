@@ -382,8 +382,38 @@ template <class M> struct ModeRep {
   }
 };
 
-template <class M>
-__device__ __forceinline__ void collide(const LatDesc& L, float d[M::Q], uint32_t site, uint32_t tlo, uint32_t thi) {
+// The collision's coefficients held in registers for a kernel that collides
+// many times in a loop: read from the descriptor there, they are scalar loads
+// that every collision waits for.
+template <class M> struct Coef {
+  static constexpr int N = M::Q - M::D - 1;
+  float ca[N], cb[M::NSTRESS], cc[N];
+  uint32_t key0, key1;
+  bool thermal, kinetic;
+  static __device__ __forceinline__ float pin(float v) {
+    asm volatile("" : "+s"(v));
+    return v;
+  }
+  __device__ __forceinline__ explicit Coef(const LatDesc& L) {
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (ModeRep<M>::of(k + M::D + 1) == k) {
+        ca[k] = pin(L.ca[k]);
+        cc[k] = pin(L.cc[k]);
+        if (k < M::NSTRESS) cb[k] = pin(L.cb[k]);
+      }
+    key0 = L.key0;
+    key1 = L.key1;
+    thermal = L.thermal != 0;
+    kinetic = L.kinetic != 0;
+  }
+  // Before each collision: the round keys are then computed anew (scalar adds
+  // beside the vector work) instead of held in 18 registers across the loop.
+  __device__ __forceinline__ void fresh_keys() { asm volatile("" : "+s"(key0), "+s"(key1)); }
+};
+
+template <class M, int S, class CF>
+__device__ __forceinline__ void collide(const CF& L, float d[M::Q], uint32_t site, uint32_t tlo, uint32_t thi) {
   constexpr int Q = M::Q, K0 = M::D + 1, NS = M::NSTRESS;
   float mu[Q];
   M::template forward<false>(d, mu);
@@ -394,8 +424,6 @@ __device__ __forceinline__ void collide(const LatDesc& L, float d[M::Q], uint32_
   M::stress_eq(mu, iR, eq);
 
   float nu[Q];
-#pragma unroll
-  for (int k = K0; k < Q; ++k) nu[k] = 0.0f;
   if (L.thermal) {
     constexpr int NP = (Q - K0 + 1) / 2;    // Box-Muller pairs
     constexpr int NT = (2 * NP + 3) / 4;    // word triples, four chunks each
@@ -413,6 +441,9 @@ __device__ __forceinline__ void collide(const LatDesc& L, float d[M::Q], uint32_
     for (int p = 0; p < NP; ++p) box_muller(ch[2 * p], ch[2 * p + 1], chunk_scale(2 * p + 1), k2, z[2 * p], z[2 * p + 1]);
 #pragma unroll
     for (int k = K0; k < Q; ++k) nu[k] = L.cc[ModeRep<M>::of(k)] * z[k - K0];
+  } else {
+#pragma unroll
+    for (int k = K0; k < Q; ++k) nu[k] = 0.0f;
   }
 #pragma unroll
   for (int k = K0; k < K0 + NS; ++k) {
@@ -429,6 +460,15 @@ __device__ __forceinline__ void collide(const LatDesc& L, float d[M::Q], uint32_
   for (int k = 1; k < K0; ++k) nu[k] = mu[k] * (1.0f / 12.0f);
 
   M::back(nu, d);
+  if constexpr (M::D == 2 && S == ST_F16) {
+    // The D2Q9 rest population ends in a multiply-add, which a conversion to
+    // fp16 may join in one rounding (v_fma_mixlo_f16) or follow with a second
+    // one; taken here, the single rounding is every kernel's.
+    _Float16 h;
+    const float rest = nu[0] - 2.0f * nu[3];
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3" : "=v"(h) : "v"(nu[8]), "s"(2.0f), "v"(rest));
+    d[0] = (float)h;
+  }
 }
 
 // ---------------------------------------------------------------- tile lookup
@@ -485,7 +525,7 @@ k_step(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, uint3
   float d[Q];
   Off o[Q];
   load_site<M, S, P, RES>(L, site, d, o);
-  collide<M>(L, d, site, (uint32_t)t, (uint32_t)(t >> 32));
+  collide<M, S>(L, d, site, (uint32_t)t, (uint32_t)(t >> 32));
   using CP = CachePolicy<M, S, P, RES>;
   using T = typename C::T;
   if constexpr (S != ST_F32 && !WIDE && P == 1) {
@@ -583,7 +623,7 @@ k_step_rows(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, 
       d[M::OPP[j]] = C::dec(v);
     }
   }
-  collide<M>(L, d, site, (uint32_t)t, (uint32_t)(t >> 32));
+  collide<M, S>(L, d, site, (uint32_t)t, (uint32_t)(t >> 32));
   // uniform row offset (elements) and lane byte offset of plane j at r + c_j
   auto row_of = [&](int j) {
     uint32_t ro = r0;
@@ -884,7 +924,7 @@ k_step2(const LatDesc* __restrict__ src, uint64_t dst_base, const uint64_t* __re
     float d[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) d[i] = C::dec(Carry<T>::unwrap(v[i]));
-    if constexpr (!PROP) collide<M>(L, d, sxy + zfirst(it) * nxy, (uint32_t)t, (uint32_t)(t >> 32));
+    if constexpr (!PROP) collide<M, S>(L, d, sxy + zfirst(it) * nxy, (uint32_t)t, (uint32_t)(t >> 32));
     const uint32_t fs = (it + 2u) % 3u, us = it % 4u, ds = it & 1u;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
@@ -906,7 +946,7 @@ k_step2(const LatDesc* __restrict__ src, uint64_t dst_base, const uint64_t* __re
     for (int i = 0; i < Q; ++i) d[i] = C::dec(h[i]);
     if constexpr (!PROP) {
       const uint64_t t1 = t + 1u;
-      collide<M>(L, d, x2 + ry + z * nxy, (uint32_t)t1, (uint32_t)(t1 >> 32));
+      collide<M, S>(L, d, x2 + ry + z * nxy, (uint32_t)t1, (uint32_t)(t1 >> 32));
     }
     if constexpr (WIDE) {  // one descriptor per z-plane of each population plane
       const uint32_t zm = z == 0 ? nz - 1u : z - 1u;
