@@ -122,7 +122,7 @@ def launch_duration(lat, reps=10):
         ev[2 * r + 1].record(lat.stream)
     torch.cuda.synchronize()
     ms = sum(ev[2 * r].elapsed_time(ev[2 * r + 1]) for r in range(reps)) / reps / 2
-    k2 = "k_strip2d" if lat.lattice == "d2q9" else "k_step2"
+    k2 = "k_strip2d" if lat.lattice == "d2q9" else "k_pass3d"
     return {"kernel": (f"{k2}<fp32/fp16/bf16> (fused pair of steps)" if fused else
                        "k_step / k_step_rows (even and odd AA steps, as scheduled)"),
             "ms": ms, "site_updates_per_launch_per_site": 2 if fused else 1,

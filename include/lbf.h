@@ -135,8 +135,8 @@ size_t lb_state_bytes(const lb_params* p);
  * (t0 >= 0); d_fields is required for LB_INIT_FIELDS and ignored otherwise.
  * The context stores p by value.  Its default schedule (lb_get_schedule)
  * depends on the state: an fp32 lattice of more than 256 MiB (D3Q19) or
- * 32 MiB (D2Q9), or a 16-bit D2Q9 one of more than 320 MB, takes the fused
- * schedule when the device has room for its second state buffer (16 bits:
+ * 32 MiB (D2Q9), or a 16-bit one of more than 320 MB that is D2Q9 or has
+ * kT = 0, takes the fused schedule when the device has room for its second state buffer (16 bits:
  * when that is at most a quarter of the free memory) and its z-planes, or
  * D2Q9 rows, hold less than 4 GiB per population; lb_init then allocates the
  * buffer (release it with lb_set_schedule and fused = 0).  With LB_BF16 storage and kT = 0

@@ -15,6 +15,7 @@
 
 #include "lbf.h"
 #include "lbf_kernels.h"
+#include "lbf_pass3d.h"
 #include "lbf_strip2d.h"
 
 using namespace lbf;
@@ -201,26 +202,27 @@ void* rows_ptr(int lattice, int storage, int parity, bool res, int block, bool p
                             : rows_ptr_m<D3Q19, false>(storage, parity, res, block);
 }
 
-// Fused passes of k steps per launch (D3Q19: k = 2, wide: planes of 4 GiB or
-// more, addressed one z-plane at a time; D2Q9: k = 2, 3 or 4) and their
-// propagation-only twins.
-template <int S>
-void* pass_ptr_s(int lattice, int k, bool wide, bool prop) {
-  if (lattice == LB_D2Q9) {
-    if (k == 4) return prop ? (void*)&k_strip2d<S, true, 4> : (void*)&k_strip2d<S, false, 4>;
-    if (k == 3) return prop ? (void*)&k_strip2d<S, true, 3> : (void*)&k_strip2d<S, false, 3>;
-    return prop ? (void*)&k_strip2d<S, true, 2> : (void*)&k_strip2d<S, false, 2>;
-  }
-  if (wide) return prop ? (void*)&k_step2<S, true, true> : (void*)&k_step2<S, false, true>;
-  return prop ? (void*)&k_step2<S, true, false> : (void*)&k_step2<S, false, false>;
+// Fused passes of k steps per launch (D3Q19: k = 2; D2Q9: k = 2, 3 or 4) and
+// their propagation-only twins.  pull, own: the D3Q19 pass reads, writes
+// populations that are not streamed yet (between the passes of one call).
+template <int S, bool PROP>
+void* pass_ptr_s(int lattice, int k, bool pull, bool own) {
+  if (lattice == LB_D2Q9)
+    return k == 4 ? (void*)&k_strip2d<S, PROP, 4> : k == 3 ? (void*)&k_strip2d<S, PROP, 3> : (void*)&k_strip2d<S, PROP, 2>;
+  if (pull) return own ? (void*)&k_pass3d<S, PROP, true, true> : (void*)&k_pass3d<S, PROP, true, false>;
+  return (void*)&k_pass3d<S, PROP, false, true>;  // the first of two passes or more
 }
-void* pass_ptr(int lattice, int storage, int k, bool wide, bool prop) {
+template <bool PROP>
+void* pass_ptr_p(int lattice, int storage, int k, bool pull, bool own) {
   switch (storage) {
-    case LB_F32: return pass_ptr_s<ST_F32>(lattice, k, wide, prop);
-    case LB_F16: return pass_ptr_s<ST_F16>(lattice, k, wide, prop);
-    case LB_BF16: return pass_ptr_s<ST_BF16>(lattice, k, wide, prop);
+    case LB_F32: return pass_ptr_s<ST_F32, PROP>(lattice, k, pull, own);
+    case LB_F16: return pass_ptr_s<ST_F16, PROP>(lattice, k, pull, own);
+    case LB_BF16: return pass_ptr_s<ST_BF16, PROP>(lattice, k, pull, own);
   }
   return nullptr;
+}
+void* pass_ptr(int lattice, int storage, int k, bool pull, bool own, bool prop) {
+  return prop ? pass_ptr_p<true>(lattice, storage, k, pull, own) : pass_ptr_p<false>(lattice, storage, k, pull, own);
 }
 
 // Initial states (rest, thermal, fields), gathers (populations, moments,
@@ -318,14 +320,12 @@ struct lb_ctx {
     uint64_t n;
   } adv_args;
 
-  // fused schedule: the second state buffer (library-owned), the descriptors
-  // of both buffers (d_f2[0] the state, d_f2[1] the second buffer), the
-  // launches of its passes and the most steps a pass takes
+  // fused schedule: the second state buffer (library-owned), the launches of
+  // its passes and the most steps a pass takes
   char* d_state_b = nullptr;
-  LatDesc* d_f2 = nullptr;
   struct PassPlan {
-    uint32_t ntx = 0, nty = 0, len = 0;  // D3Q19 tiles
-    StripGeom strip{};                   // D2Q9 strips
+    PassGeom tiles{};   // D3Q19
+    StripGeom strip{};  // D2Q9
     uint32_t grid = 0;
     int threads = 0;
   };
@@ -333,15 +333,15 @@ struct lb_ctx {
   int pass_max = 2;
   struct PassArgs {
     const LatDesc* src;
-    uint64_t dst;
     PassSide from, to;
     const uint64_t* d_t;
-    uint32_t t_off, ntx, nty, zlen;
+    uint32_t t_off;
+    PassGeom tiles;
     StripGeom strip;
+    void* fn;
     // the kernel's arguments in order
     std::vector<void*> list(int lattice) {
-      if (lattice == LB_D2Q9) return {&src, &from, &to, &d_t, &t_off, &strip};
-      return {&src, &dst, &d_t, &t_off, &ntx, &nty, &zlen};
+      return {&src, &from, &to, &d_t, &t_off, lattice == LB_D2Q9 ? (void*)&strip : (void*)&tiles};
     }
   };
   std::vector<PassArgs> graph_pass_args;
@@ -358,20 +358,20 @@ void drop_graph(lb_ctx* c) {
   c->graph = nullptr;
 }
 
-// Planes per tile column of the D3Q19 fused pass,
-// for `across` tiles per plane, `extent` planes and `slots` tiles resident
-// on the device at a time (CUs times tiles per CU).  A pass runs in rounds
-// of `slots` tiles, each round taking one tile's chunk + 3 phases plus about
-// one of set-up.  Lattices with many rounds take 32 planes (the fastest at
-// 512^3); with few, a last round that leaves many CUs idle costs
-// a large part of the pass, and the chunk length from 8 to 32 that
-// minimises the estimate is taken instead (256^3 on 256 CUs: 22 planes, 5
-// rounds of 26 phases instead of 4 of 36).  The result does not depend on it.
+// Planes per tile column of the D3Q19 fused pass, for `across` tiles per
+// plane, `extent` planes and `slots` tiles resident on the device at a time
+// (CUs times tiles per CU).  A pass runs in rounds of `slots` tiles, each round
+// taking one tile's chunk + 2 phases (its halo planes) plus about one of
+// set-up; the chunk length from 8 to 128 that minimises the estimate is taken.
+// Long chunks collide fewer halo planes (512^3 fp32, us per step: 16 planes
+// 2487, 32 2386, 64 2325, 128 2305), but a last round that leaves many CUs
+// idle costs a large part of a pass (256 planes 2651; 256^3: 43 planes, two
+// rounds nearly full, 308, 64 planes 403; 160^3: 27 planes 96, 20 planes 128).
+// The result does not depend on it.
 uint32_t fused_chunk(uint64_t across, uint32_t extent, uint32_t slots) {
-  constexpr uint32_t LONG = 32;
+  constexpr uint32_t LONG = 128;
   auto tiles = [&](uint32_t z) { return across * ((extent + z - 1u) / z); };
-  auto cost = [&](uint32_t z) { return ((tiles(z) + slots - 1u) / slots) * (uint64_t)(z + 4u); };
-  if (tiles(LONG) >= 16ull * slots) return LONG;
+  auto cost = [&](uint32_t z) { return ((tiles(z) + slots - 1u) / slots) * (uint64_t)(z + 3u); };
   uint32_t best = LONG;
   for (uint32_t z = 8; z < LONG; ++z)
     if (cost(z) < cost(best)) best = z;
@@ -396,10 +396,9 @@ int plan_passes(lb_ctx* c) {
   c->pass_max = 2;
   for (int k = 2; k <= (c->lattice == LB_D2Q9 ? 4 : 2); ++k) {
     lb_ctx::PassPlan& p = c->plans[k - 2];
-    p.threads = c->lattice == LB_D2Q9 ? 64 * S2_WAVES : F2_THREADS;
+    p.threads = c->lattice == LB_D2Q9 ? 64 * S2_WAVES : P3_THREADS;
     int per_cu = 0;
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pass_ptr(c->lattice, c->storage, k, c->wide, false),
-                                                         p.threads, 0));
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pass_ptr(c->lattice, c->storage, k, true, true, false), p.threads, 0));
     const uint32_t slots = (uint32_t)std::max(1, cus * per_cu);  // workgroups resident at a time
     if (c->lattice == LB_D2Q9) {
       StripGeom& g = p.strip;
@@ -414,10 +413,13 @@ int plan_passes(lb_ctx* c) {
       // 2048^2, 15 rows: 34.0 and 37.9).
       if (k == 4 && g.len >= 8) c->pass_max = 4;
     } else {
-      p.ntx = (L.nx + 63u) / 64u;
-      p.nty = (L.ny + (uint32_t)F2_TY - 1u) / (uint32_t)F2_TY;
-      p.len = fused_chunk((uint64_t)p.ntx * p.nty, L.nz, slots);
-      p.grid = p.ntx * p.nty * ((L.nz + p.len - 1u) / p.len);
+      PassGeom& g = p.tiles;
+      g.ntx = (L.nx + (uint32_t)P3_TX - 1u) / (uint32_t)P3_TX;
+      g.nty = (L.ny + (uint32_t)P3_TY - 1u) / (uint32_t)P3_TY;
+      g.tx = P3_TX;
+      g.ty = P3_TY;
+      g.len = fused_chunk((uint64_t)g.ntx * g.nty, L.nz, slots);
+      p.grid = g.ntx * g.nty * ((L.nz + g.len - 1u) / g.len);
     }
   }
   return LB_OK;
@@ -471,10 +473,6 @@ int upload_schedule(lb_ctx* c) {
   HIP_TRY(hipMemcpy(c->d_blk, blk.data(), sizeof(uint32_t) * (nlat + 1), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(c->d_blk_rows, blk_rows.data(), sizeof(uint32_t) * (nlat + 1), hipMemcpyHostToDevice));
   if (c->sched.fused) {
-    // descriptors of the state buffer and of the second buffer (same geometry)
-    LatDesc f2[2] = {c->lats[0], c->lats[0]};
-    f2[1].base = (uint64_t)(uintptr_t)c->d_state_b;
-    HIP_TRY(hipMemcpy(c->d_f2, f2, sizeof(f2), hipMemcpyHostToDevice));
     const int rc = plan_passes(c);
     if (rc) return rc;
   }
@@ -572,32 +570,34 @@ std::vector<int> pass_steps(const lb_ctx* c, int64_t m) {
   return ks;
 }
 
-// One pass of k steps from even t + t_off: state buffer -> second buffer
-// (to_b) or back.
-lb_ctx::PassArgs pass_args(const lb_ctx* c, uint32_t t_off, bool to_b, int k) {
+// Pass n of ks, the first of which starts at even t + t_off: state buffer ->
+// second buffer (n even) or back.  The second buffer holds the q populations of
+// an x-row side by side (see k_pass3d) where a slice of it (a z-plane, a D2Q9
+// row) fits the range of a buffer descriptor.
+lb_ctx::PassArgs pass_args(const lb_ctx* c, uint32_t t_off, const std::vector<int>& ks, size_t n, bool prop) {
   const LatDesc& L = c->lats[0];
-  const lb_ctx::PassPlan& p = c->plans[k - 2];
-  const uint64_t b = (uint64_t)(uintptr_t)c->d_state_b;
-  const uint32_t es = (uint32_t)elem_size(c->storage), row = L.nx * es;
-  const PassSide A{L.base, L.plane * es, row, row};
+  const lb_ctx::PassPlan& p = c->plans[ks[n] - 2];
+  const uint32_t row = L.nx * (uint32_t)elem_size(c->storage);
+  const uint32_t slice = c->lattice == LB_D2Q9 ? row : row * L.ny;
+  const PassSide A{L.base, L.plane * elem_size(c->storage), slice, row, slice};
   PassSide B = A;
-  B.base = b;
-  // the second D2Q9 buffer holds the nine populations of a row side by side
-  // (see k_strip2d) where such a row fits the range of a buffer descriptor
-  const uint64_t q = (uint64_t)q_of(c->lattice);
-  if (q * row < (1ull << 32)) {
+  B.base = (uint64_t)(uintptr_t)c->d_state_b;
+  const uint32_t q = (uint32_t)q_of(c->lattice);
+  if ((uint64_t)q * slice < (1ull << 32)) {
     B.plane = row;
-    B.slice = B.span = (uint32_t)q * row;
+    B.row = q * row;
+    B.slice = B.span = q * slice;
   }
-  return {to_b || c->lattice == LB_D2Q9 ? c->d_f2 : c->d_f2 + 1, to_b ? b : L.base, to_b ? A : B, to_b ? B : A,
-          c->d_t, t_off, p.ntx, p.nty, p.len, p.strip};
+  const bool to_b = (n & 1) == 0;
+  for (size_t j = 0; j < n; ++j) t_off += (uint32_t)ks[j];
+  return {c->d_lats, to_b ? A : B, to_b ? B : A, c->d_t, t_off, p.tiles, p.strip,
+          pass_ptr(c->lattice, c->storage, ks[n], n > 0, n + 1 < ks.size(), prop)};
 }
 
-int launch_pass(lb_ctx* c, uint32_t t_off, bool to_b, int k, bool prop = false) {
-  lb_ctx::PassArgs a = pass_args(c, t_off, to_b, k);
-  const lb_ctx::PassPlan& p = c->plans[k - 2];
-  HIP_TRY(hipLaunchKernel(pass_ptr(c->lattice, c->storage, k, c->wide, prop), dim3(p.grid), dim3(p.threads),
-                          a.list(c->lattice).data(), 0, c->stream));
+int launch_pass(lb_ctx* c, uint32_t t_off, const std::vector<int>& ks, size_t n, bool prop) {
+  lb_ctx::PassArgs a = pass_args(c, t_off, ks, n, prop);
+  const lb_ctx::PassPlan& p = c->plans[ks[n] - 2];
+  HIP_TRY(hipLaunchKernel(a.fn, dim3(p.grid), dim3(p.threads), a.list(c->lattice).data(), 0, c->stream));
   return LB_OK;
 }
 
@@ -635,14 +635,12 @@ int build_graph(lb_ctx* c) {
     prev = node;
     return LB_OK;
   };
-  uint32_t at = 0;
   for (size_t n = 0; n < ks.size(); ++n) {
-    c->graph_pass_args[n] = pass_args(c, at, (n & 1) == 0, ks[n]);
+    lb_ctx::PassArgs& a = c->graph_pass_args[n];
+    a = pass_args(c, 0, ks, n, false);
     const lb_ctx::PassPlan& p = c->plans[ks[n] - 2];
-    int rc = add_node(pass_ptr(c->lattice, c->storage, ks[n], c->wide, false), p.grid, p.threads,
-                      c->graph_pass_args[n].list(c->lattice).data());
+    int rc = add_node(a.fn, p.grid, p.threads, a.list(c->lattice).data());
     if (rc) return rc;
-    at += (uint32_t)ks[n];
   }
   const int K1 = K - covered;  // AA steps per group, from step `covered` of the chunk
   for (size_t n = 0; n < c->graph_args.size(); ++n) {
@@ -670,12 +668,11 @@ int build_graph(lb_ctx* c) {
 int direct_steps(lb_ctx* c, int64_t m, bool prop = false) {
   int64_t s = 0;
   if (c->sched.fused && !(c->t & 1)) {
-    bool to_b = true;
-    for (int k : pass_steps(c, m)) {
-      int rc = launch_pass(c, (uint32_t)s, to_b, k, prop);
+    const std::vector<int> ks = pass_steps(c, m);
+    for (size_t n = 0; n < ks.size(); ++n) {
+      int rc = launch_pass(c, 0, ks, n, prop);
       if (rc) return rc;
-      s += k;
-      to_b = !to_b;
+      s += ks[n];
     }
   }
   for (; s < m; ++s) {
@@ -732,8 +729,7 @@ int alloc_meta(lb_ctx* c) {
   const size_t lats = sizeof(LatDesc) * nlat;
   const size_t blk = sizeof(uint32_t) * (nlat + 1);
   auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
-  const size_t f2 = up(2 * sizeof(LatDesc));
-  const size_t total = head + up(part) + 2 * up(lats) + 2 * up(blk) + f2;
+  const size_t total = head + up(part) + 2 * up(lats) + 2 * up(blk);
   HIP_TRY(hipMalloc(&c->d_meta, total));
   c->d_t = reinterpret_cast<uint64_t*>(c->d_meta);
   c->d_result = reinterpret_cast<double*>(c->d_meta + 64);
@@ -742,7 +738,6 @@ int alloc_meta(lb_ctx* c) {
   c->d_tile_lats = reinterpret_cast<LatDesc*>(c->d_meta + head + up(part) + up(lats));
   c->d_blk = reinterpret_cast<uint32_t*>(c->d_meta + head + up(part) + 2 * up(lats));
   c->d_blk_rows = reinterpret_cast<uint32_t*>(c->d_meta + head + up(part) + 2 * up(lats) + up(blk));
-  c->d_f2 = reinterpret_cast<LatDesc*>(c->d_meta + head + up(part) + 2 * up(lats) + 2 * up(blk));
   HIP_TRY(hipHostMalloc((void**)&c->h_result, sizeof(double) * 5, hipHostMallocDefault));
   HIP_TRY(hipMemcpy(c->d_lats, c->lats.data(), lats, hipMemcpyHostToDevice));
   return LB_OK;
@@ -842,18 +837,20 @@ int default_schedule(lb_ctx* c) {
   // Measured crossovers of fp32 against the resident AA steps: D3Q19 between
   // 152^3 (267 MB, AA 8% faster) and 156^3 (289 MB, fused 13% faster), D2Q9
   // between 724^2 (19 MB, AA 6% faster) and 1024^2 (38 MB, fused 7% faster).
-  // 16-bit D2Q9 state takes them above the resident band (16384^2 bf16: 1.49
-  // against 1.76 ms per step; 4096^2, inside it, 108 against 118 us; 2048^2 36
-  // against 31).  16-bit D3Q19 state keeps one step per launch: its collision
-  // already keeps the VALU busy enough that the fused pass is slower.
-  const bool d2 = c->lattice == LB_D2Q9;
-  const uint64_t fused_above = d2 ? (c->storage == LB_F32 ? 32 * MIB : 320 * MB) : 256 * MIB;
-  if ((d2 || c->storage == LB_F32) && fused_eligible(c) && total > fused_above) {
+  // 16-bit D2Q9 state takes them above the resident band (16384^2 bf16: 1.55
+  // against 1.84 ms per step; 4096^2, inside it, 111 against 118 us; 2048^2 36
+  // against 31).  So does 16-bit D3Q19 state without noise (512^3 fp16 1.45
+  // against 1.96 ms; 256^3 192 against 208 us); with noise the collisions bound
+  // the pass (512^3 fp16 1.99 against 1.85 ms) and it keeps one step per launch.
+  const bool d2 = c->lattice == LB_D2Q9, f32 = c->storage == LB_F32;
+  const uint64_t fused_above = f32 ? (d2 ? 32 * MIB : 256 * MIB) : 320 * MB;
+  const bool pays = d2 || f32 || c->reps[0].kT == 0.0;
+  if (pays && fused_eligible(c) && total > fused_above) {
     const std::string keep = g_last_error;
     size_t free_b = 0, total_b = 0;
     // 16-bit state: only where the second buffer is a small part of what is
     // free, so that large 16-bit lattices keep the memory they are chosen for
-    const bool room = c->storage == LB_F32 || (hipMemGetInfo(&free_b, &total_b) == hipSuccess && 4 * total <= free_b);
+    const bool room = f32 || (hipMemGetInfo(&free_b, &total_b) == hipSuccess && 4 * total <= free_b);
     if (room && ensure_state_b(c) == LB_OK) c->sched.fused = 1;
     else g_last_error = keep;  // no room: one step per launch, not an error
   }

@@ -40,13 +40,6 @@
 
 namespace lbf {
 
-// One side of a pass: population i of site (x, y) lies base + i plane +
-// y slice + x elements; span bytes of a slice are addressed at a time.
-struct PassSide {
-  uint64_t base, plane;
-  uint32_t slice, span;
-};
-
 struct StripGeom {
   uint32_t ntx;  // strips along x
   uint32_t tx;   // interior sites of a strip, at most 64 - 2 (K - 1)
@@ -109,15 +102,12 @@ k_strip2d(const LatDesc* __restrict__ src, PassSide from, PassSide to, const uin
   const uint32_t so = mine ? vo : NOWHERE, som = mine ? xm * ES : NOWHERE, sop = mine ? xp * ES : NOWHERE;
 
   auto next = [&](uint32_t y) { return y + 1u >= ny ? 0u : y + 1u; };
-  auto rsrc_at = [&](uint64_t a, uint32_t span) {
-    return __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)a, 0, (int)span, RAW_BUFFER_WORD3);
-  };
   auto load_row = [&](uint32_t y, uint32_t v_off, U (&v)[Q]) {
     uint64_t a = from.base + (uint64_t)y * from.slice;
     asm volatile("" : "+s"(a));
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-      v[i] = Carry<T>::wrap(Raw<T>::template ld<0>(rsrc_at(a, from.span), v_off, 0u));
+      v[i] = Carry<T>::wrap(Raw<T>::template ld<0>(span_rsrc(a, from.span), v_off));
       a += from.plane;
     }
   };
@@ -132,8 +122,8 @@ k_strip2d(const LatDesc* __restrict__ src, PassSide from, PassSide to, const uin
     for (int j = 0; j < Q; ++j) {
       T o;
       if constexpr (PROP) o = h[j]; else o = C::enc(h[j]);
-      Raw<T>::template st<0>(rsrc_at(a + (M::CY[j] > 0 ? op : (M::CY[j] < 0 ? om : o0)), to.span),
-                             M::CX[j] > 0 ? vp : (M::CX[j] < 0 ? vm : v0), o, 0u);
+      Raw<T>::template st<0>(span_rsrc(a + (M::CY[j] > 0 ? op : (M::CY[j] < 0 ? om : o0)), to.span),
+                             M::CX[j] > 0 ? vp : (M::CX[j] < 0 ? vm : v0), o);
       a += to.plane;
     }
   };
