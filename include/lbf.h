@@ -139,7 +139,11 @@ size_t lb_state_bytes(const lb_params* p);
  * kT = 0, takes the fused schedule when the device has room for its second state buffer (16 bits:
  * when that is at most a quarter of the free memory) and its z-planes, or
  * D2Q9 rows, hold less than 4 GiB per population; lb_init then allocates the
- * buffer (release it with lb_set_schedule and fused = 0).  With LB_BF16 storage and kT = 0
+ * buffer (release it with lb_set_schedule and fused = 0).  Small lattices
+ * (D3Q19 of up to 16384 sites, D2Q9 of up to 16 MB in fp32 or 5 MB in 16 bits)
+ * report fused = 0 and, until lb_set_schedule or lb_autotune, advance by
+ * several steps per launch all the same, through a buffer of that size which
+ * belongs to the context.  With LB_BF16 storage and kT = 0
  * it succeeds and leaves a warning in lb_last_error(). */
 int lb_init(const lb_params* p, void* d_state, void* hip_stream, int32_t init_kind,
             const float* d_fields, int64_t t0, lb_ctx** out);
@@ -263,7 +267,7 @@ typedef struct {
                         /* steps of one group before the next.  Replicas are   */
                         /* independent, so results do not depend on it.        */
   int32_t fused;        /* 0: one in-place AA launch per step.  1: several     */
-                        /* steps per launch (D3Q19 two, D2Q9 two to four):     */
+                        /* steps per launch (two to eight):                    */
                         /* from even t, each launch reads the state once and   */
                         /* writes the state those steps later into a second    */
                         /* buffer that the library allocates                   */

@@ -15,6 +15,7 @@
 
 #include "lbf.h"
 #include "lbf_kernels.h"
+#include "lbf_block.h"
 #include "lbf_pass3d.h"
 #include "lbf_strip2d.h"
 
@@ -225,6 +226,26 @@ void* pass_ptr(int lattice, int storage, int k, bool pull, bool own, bool prop) 
   return prop ? pass_ptr_p<true>(lattice, storage, k, pull, own) : pass_ptr_p<false>(lattice, storage, k, pull, own);
 }
 
+// Fused passes of small lattices, by the lanes of a workgroup.
+template <class M, int S, bool PROP>
+void* block_ptr_s(int lanes) {
+  return lanes <= 256 ? (void*)&k_block<M, S, PROP, 256>
+                      : lanes <= 512 ? (void*)&k_block<M, S, PROP, 512> : (void*)&k_block<M, S, PROP, 1024>;
+}
+template <class M, bool PROP>
+void* block_ptr_m(int storage, int lanes) {
+  switch (storage) {
+    case LB_F32: return block_ptr_s<M, ST_F32, PROP>(lanes);
+    case LB_F16: return block_ptr_s<M, ST_F16, PROP>(lanes);
+    case LB_BF16: return block_ptr_s<M, ST_BF16, PROP>(lanes);
+  }
+  return nullptr;
+}
+void* block_ptr(int lattice, int storage, int lanes, bool prop) {
+  if (lattice == LB_D2Q9) return prop ? block_ptr_m<D2Q9, true>(storage, lanes) : block_ptr_m<D2Q9, false>(storage, lanes);
+  return prop ? block_ptr_m<D3Q19, true>(storage, lanes) : block_ptr_m<D3Q19, false>(storage, lanes);
+}
+
 // Initial states (rest, thermal, fields), gathers (populations, moments,
 // modes) and the health check; init and gather kinds are template
 // parameters of their kernels.
@@ -326,11 +347,19 @@ struct lb_ctx {
   struct PassPlan {
     PassGeom tiles{};   // D3Q19
     StripGeom strip{};  // D2Q9
-    uint32_t grid = 0;
+    BlockGeom block{};  // small lattices
+    dim3 grid;
     int threads = 0;
   };
-  PassPlan plans[3];  // passes of 2, 3 and 4 steps
+  static constexpr int PASS_MAX = 8;
+  PassPlan plans[PASS_MAX + 1];  // by the steps of a pass, from 2
   int pass_max = 2;
+  bool blocks = false;           // small lattice: every pass is k_block
+  // Small lattices run passes of several steps before any schedule is set,
+  // through a second buffer of their own in d_meta.
+  char* d_small_b = nullptr;
+  bool small_passes = false;
+  bool passes(bool prop) const { return sched.fused || (small_passes && !prop); }
   struct PassArgs {
     const LatDesc* src;
     PassSide from, to;
@@ -338,9 +367,12 @@ struct lb_ctx {
     uint32_t t_off;
     PassGeom tiles;
     StripGeom strip;
+    BlockGeom block;
+    uint64_t t_off64;
     void* fn;
     // the kernel's arguments in order
     std::vector<void*> list(int lattice) {
+      if (block.steps) return {&src, &d_t, &t_off64, &block};
       return {&src, &from, &to, &d_t, &t_off, lattice == LB_D2Q9 ? (void*)&strip : (void*)&tiles};
     }
   };
@@ -388,14 +420,92 @@ uint32_t strip_rows(uint32_t across, uint32_t extent, uint32_t slots) {
   return (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, rows));
 }
 
+// Whether the passes over a lattice are k_block's: D2Q9 of up to 64 MB (1024^2
+// fp32, 38 MB: 10.6 us per step, strips 11.7; 2048^2: 34.3 and 32.8) and D3Q19
+// of up to 16384 sites (beyond, the AA steps are as fast: 24^3 fp32 4.0 against
+// 4.3 us, 32^3 5.6 against 4.6).
+bool block_passes(const lb_params& p) {
+  if (p.lattice == LB_D2Q9) return sites_of(p) * D2Q9::Q * elem_size(p.storage) <= 64000000ull;
+  return sites_of(p) <= 16384;
+}
+
+// Bytes of the second buffer of a small lattice, which takes several steps per
+// launch (k_block) by default: D3Q19 of up to 16384 sites (16^3 fp32 3.2 us per
+// step, AA 3.9), D2Q9 of up to 16 MB in fp32 (64 x 48 1.75 against 3.5 us,
+// 512^2 4.4 against 5.5) and 5 MB in 16 bits (512^2 bf16 4.7 against 4.8; 1024^2
+// 11.4 against 11.3).  0 for a larger lattice or a batch.
+size_t small_bytes(const lb_ctx* c) {
+  if (c->reps.size() != 1) return 0;
+  const lb_params& p = c->reps[0];
+  const size_t bytes = (size_t)q_of(p.lattice) * sites_of(p) * elem_size(p.storage);
+  if (p.lattice == LB_D2Q9) return bytes <= (p.storage == LB_F32 ? 16000000u : 5000000u) ? bytes : 0;
+  return block_passes(p) ? bytes : 0;
+}
+
+// Blocks of k_block and the most steps a pass of them takes.  D2Q9: 58 x 10
+// sites (one wave a row at four steps) where that makes 128 workgroups or more
+// (256^2 fp32 2.9 us per step, with 8 x 8 3.5; 1024^2 10.6 and 19.2), else 16 x
+// 16, else 8 x 8, which spreads the smallest lattices over more compute units
+// (64 x 48: 1.9 us, with 58 x 10 2.4) and, while there are few of them, takes
+// eight steps a pass (1.75).  D3Q19: 4^3 and three steps (16^3 fp32 3.2 us, with
+// two steps 3.6, 8 x 8 x 4 and two 4.1; AA 3.9).  Blocks split the lattice
+// evenly.
+void plan_blocks(lb_ctx* c) {
+  const LatDesc& L = c->lats[0];
+  const bool d2 = c->lattice == LB_D2Q9;
+  auto blocks = [](uint32_t n, uint32_t b) { return (n + b - 1u) / b; };
+  uint32_t b[3] = {4, 4, 4};
+  c->pass_max = 3;
+  if (d2) {
+    constexpr uint32_t SIZES[3][2] = {{58, 10}, {16, 16}, {8, 8}};
+    uint32_t count = 0;
+    b[2] = 1;
+    for (const auto& sz : SIZES) {
+      b[0] = sz[0];
+      b[1] = sz[1];
+      count = blocks(L.nx, b[0]) * blocks(L.ny, b[1]);
+      if (count >= 128) break;
+    }
+    c->pass_max = count <= 64 ? 8 : 4;
+  }
+  b[0] = blocks(L.nx, blocks(L.nx, b[0]));
+  b[1] = blocks(L.ny, blocks(L.ny, b[1]));
+  b[2] = blocks(L.nz, blocks(L.nz, b[2]));
+  for (int k = 2; k <= c->pass_max; ++k) {
+    lb_ctx::PassPlan& p = c->plans[k];
+    BlockGeom& g = p.block;
+    const uint32_t h = 2u * (uint32_t)(k - 1);
+    g.nx = L.nx;
+    g.ny = L.ny;
+    g.nz = L.nz;
+    g.bx = b[0];
+    g.by = b[1];
+    g.bz = b[2];
+    g.rx = b[0] + h;
+    g.rxy = g.rx * (b[1] + h);
+    g.mx = ((1u << 20) + g.rx - 1u) / g.rx;
+    g.mxy = ((1u << 20) + g.rxy - 1u) / g.rxy;
+    g.steps = (uint32_t)k;
+    const uint32_t lanes = g.rxy * (d2 ? 1u : b[2] + h);  // at most 64 x 16, 22 x 22 (8 x 8, eight steps), 8^3
+    p.threads = (int)((lanes + 63u) / 64u * 64u);
+    p.grid = dim3(blocks(L.nx, b[0]), blocks(L.ny, b[1]), blocks(L.nz, b[2]));
+  }
+}
+
 // Tiles of the passes over the lattice of c (CUs: the device's).
 int plan_passes(lb_ctx* c) {
   const LatDesc& L = c->lats[0];
   int cus = 0;
   HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
+  for (auto& p : c->plans) p = lb_ctx::PassPlan{};
+  c->blocks = block_passes(c->reps[0]);
+  if (c->blocks) {
+    plan_blocks(c);
+    return LB_OK;
+  }
   c->pass_max = 2;
   for (int k = 2; k <= (c->lattice == LB_D2Q9 ? 4 : 2); ++k) {
-    lb_ctx::PassPlan& p = c->plans[k - 2];
+    lb_ctx::PassPlan& p = c->plans[k];
     p.threads = c->lattice == LB_D2Q9 ? 64 * S2_WAVES : P3_THREADS;
     int per_cu = 0;
     HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pass_ptr(c->lattice, c->storage, k, true, true, false), p.threads, 0));
@@ -407,7 +517,7 @@ int plan_passes(lb_ctx* c) {
       g.tx = (L.nx + g.ntx - 1u) / g.ntx;
       g.len = strip_rows(g.ntx, L.ny, slots * S2_WAVES);
       g.nty = (L.ny + g.len - 1u) / g.len;
-      p.grid = (g.ntx * g.nty + S2_WAVES - 1u) / S2_WAVES;
+      p.grid = dim3((g.ntx * g.nty + S2_WAVES - 1u) / S2_WAVES);
       // Strips of few rows spend more on the wider halo of four steps than
       // they save (1024^2 fp32, 4 rows: 14.2 us per step, with two 12.9;
       // 2048^2, 15 rows: 34.0 and 37.9).
@@ -419,7 +529,7 @@ int plan_passes(lb_ctx* c) {
       g.tx = P3_TX;
       g.ty = P3_TY;
       g.len = fused_chunk((uint64_t)g.ntx * g.nty, L.nz, slots);
-      p.grid = g.ntx * g.nty * ((L.nz + g.len - 1u) / g.len);
+      p.grid = dim3(g.ntx * g.nty * ((L.nz + g.len - 1u) / g.len));
     }
   }
   return LB_OK;
@@ -472,7 +582,7 @@ int upload_schedule(lb_ctx* c) {
   HIP_TRY(hipMemcpy(c->d_tile_lats, tl.data(), sizeof(LatDesc) * nlat, hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(c->d_blk, blk.data(), sizeof(uint32_t) * (nlat + 1), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(c->d_blk_rows, blk_rows.data(), sizeof(uint32_t) * (nlat + 1), hipMemcpyHostToDevice));
-  if (c->sched.fused) {
+  if (c->passes(false)) {
     const int rc = plan_passes(c);
     if (rc) return rc;
   }
@@ -576,12 +686,12 @@ std::vector<int> pass_steps(const lb_ctx* c, int64_t m) {
 // row) fits the range of a buffer descriptor.
 lb_ctx::PassArgs pass_args(const lb_ctx* c, uint32_t t_off, const std::vector<int>& ks, size_t n, bool prop) {
   const LatDesc& L = c->lats[0];
-  const lb_ctx::PassPlan& p = c->plans[ks[n] - 2];
+  const lb_ctx::PassPlan& p = c->plans[ks[n]];
   const uint32_t row = L.nx * (uint32_t)elem_size(c->storage);
   const uint32_t slice = c->lattice == LB_D2Q9 ? row : row * L.ny;
   const PassSide A{L.base, L.plane * elem_size(c->storage), slice, row, slice};
   PassSide B = A;
-  B.base = (uint64_t)(uintptr_t)c->d_state_b;
+  B.base = (uint64_t)(uintptr_t)(c->sched.fused ? c->d_state_b : c->d_small_b);
   const uint32_t q = (uint32_t)q_of(c->lattice);
   if ((uint64_t)q * slice < (1ull << 32)) {
     B.plane = row;
@@ -590,14 +700,18 @@ lb_ctx::PassArgs pass_args(const lb_ctx* c, uint32_t t_off, const std::vector<in
   }
   const bool to_b = (n & 1) == 0;
   for (size_t j = 0; j < n; ++j) t_off += (uint32_t)ks[j];
-  return {c->d_lats, to_b ? A : B, to_b ? B : A, c->d_t, t_off, p.tiles, p.strip,
-          pass_ptr(c->lattice, c->storage, ks[n], n > 0, n + 1 < ks.size(), prop)};
+  BlockGeom bg = p.block;
+  bg.from = to_b ? A.base : B.base;
+  bg.to = to_b ? B.base : A.base;
+  return {c->d_lats, to_b ? A : B, to_b ? B : A, c->d_t, t_off, p.tiles, p.strip, bg, t_off,
+          c->blocks ? block_ptr(c->lattice, c->storage, p.threads, prop)
+                    : pass_ptr(c->lattice, c->storage, ks[n], n > 0, n + 1 < ks.size(), prop)};
 }
 
 int launch_pass(lb_ctx* c, uint32_t t_off, const std::vector<int>& ks, size_t n, bool prop) {
   lb_ctx::PassArgs a = pass_args(c, t_off, ks, n, prop);
-  const lb_ctx::PassPlan& p = c->plans[ks[n] - 2];
-  HIP_TRY(hipLaunchKernel(a.fn, dim3(p.grid), dim3(p.threads), a.list(c->lattice).data(), 0, c->stream));
+  const lb_ctx::PassPlan& p = c->plans[ks[n]];
+  HIP_TRY(hipLaunchKernel(a.fn, p.grid, dim3(p.threads), a.list(c->lattice).data(), 0, c->stream));
   return LB_OK;
 }
 
@@ -615,17 +729,17 @@ int launch_advance(lb_ctx* c, uint64_t n) {
 int build_graph(lb_ctx* c) {
   drop_graph(c);
   const int K = c->sched.graph_chunk;
-  const std::vector<int> ks = c->sched.fused ? pass_steps(c, K) : std::vector<int>();
+  const std::vector<int> ks = c->passes(false) ? pass_steps(c, K) : std::vector<int>();
   int covered = 0;
   for (int k : ks) covered += k;
   HIP_TRY(hipGraphCreate(&c->graph, 0));
   c->graph_args.assign((K - covered) * c->groups.size(), {});
   c->graph_pass_args.assign(ks.size(), {});
   hipGraphNode_t prev = nullptr;
-  auto add_node = [&](void* fn, uint32_t grid, int block, void** args) -> int {
+  auto add_node = [&](void* fn, dim3 grid, int block, void** args) -> int {
     hipKernelNodeParams kp{};
     kp.func = fn;
-    kp.gridDim = dim3(grid);
+    kp.gridDim = grid;
     kp.blockDim = dim3(block);
     kp.sharedMemBytes = 0;
     kp.kernelParams = args;
@@ -638,7 +752,7 @@ int build_graph(lb_ctx* c) {
   for (size_t n = 0; n < ks.size(); ++n) {
     lb_ctx::PassArgs& a = c->graph_pass_args[n];
     a = pass_args(c, 0, ks, n, false);
-    const lb_ctx::PassPlan& p = c->plans[ks[n] - 2];
+    const lb_ctx::PassPlan& p = c->plans[ks[n]];
     int rc = add_node(a.fn, p.grid, p.threads, a.list(c->lattice).data());
     if (rc) return rc;
   }
@@ -651,12 +765,12 @@ int build_graph(lb_ctx* c) {
     c->graph_args[n] = {sl.lats, sl.blk, sl.nlat, (uint32_t)c->sched.xcd_remap[s & 1], c->d_t, (uint32_t)s};
     lb_ctx::StepArgs& a = c->graph_args[n];
     void* args[] = {&a.lats, &a.blk, &a.nlat, &a.remap, &a.d_t, &a.t_off};
-    int rc = add_node(sl.fn, sl.grid, sl.block, args);
+    int rc = add_node(sl.fn, dim3(sl.grid), sl.block, args);
     if (rc) return rc;
   }
   c->adv_args = {c->d_t, (uint64_t)K};
   void* aargs[] = {&c->adv_args.d_t, &c->adv_args.n};
-  int rc = add_node((void*)&k_advance, 1, 64, aargs);
+  int rc = add_node((void*)&k_advance, dim3(1), 64, aargs);
   if (rc) return rc;
   HIP_TRY(hipGraphInstantiate(&c->graph_exec, c->graph, nullptr, nullptr, 0));
   return LB_OK;
@@ -667,7 +781,7 @@ int build_graph(lb_ctx* c) {
 // passes (out to the second buffer and back) cover all but the last steps.
 int direct_steps(lb_ctx* c, int64_t m, bool prop = false) {
   int64_t s = 0;
-  if (c->sched.fused && !(c->t & 1)) {
+  if (c->passes(prop) && !(c->t & 1)) {
     const std::vector<int> ks = pass_steps(c, m);
     for (size_t n = 0; n < ks.size(); ++n) {
       int rc = launch_pass(c, 0, ks, n, prop);
@@ -729,7 +843,8 @@ int alloc_meta(lb_ctx* c) {
   const size_t lats = sizeof(LatDesc) * nlat;
   const size_t blk = sizeof(uint32_t) * (nlat + 1);
   auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
-  const size_t total = head + up(part) + 2 * up(lats) + 2 * up(blk);
+  const size_t small = small_bytes(c), small_off = head + up(part) + 2 * up(lats) + 2 * up(blk);
+  const size_t total = small_off + small;
   HIP_TRY(hipMalloc(&c->d_meta, total));
   c->d_t = reinterpret_cast<uint64_t*>(c->d_meta);
   c->d_result = reinterpret_cast<double*>(c->d_meta + 64);
@@ -738,6 +853,7 @@ int alloc_meta(lb_ctx* c) {
   c->d_tile_lats = reinterpret_cast<LatDesc*>(c->d_meta + head + up(part) + up(lats));
   c->d_blk = reinterpret_cast<uint32_t*>(c->d_meta + head + up(part) + 2 * up(lats));
   c->d_blk_rows = reinterpret_cast<uint32_t*>(c->d_meta + head + up(part) + 2 * up(lats) + up(blk));
+  if (small) c->d_small_b = c->d_meta + small_off;
   HIP_TRY(hipHostMalloc((void**)&c->h_result, sizeof(double) * 5, hipHostMallocDefault));
   HIP_TRY(hipMemcpy(c->d_lats, c->lats.data(), lats, hipMemcpyHostToDevice));
   return LB_OK;
@@ -845,6 +961,7 @@ int default_schedule(lb_ctx* c) {
   const bool d2 = c->lattice == LB_D2Q9, f32 = c->storage == LB_F32;
   const uint64_t fused_above = f32 ? (d2 ? 32 * MIB : 256 * MIB) : 320 * MB;
   const bool pays = d2 || f32 || c->reps[0].kT == 0.0;
+  c->small_passes = c->d_small_b != nullptr;
   if (pays && fused_eligible(c) && total > fused_above) {
     const std::string keep = g_last_error;
     size_t free_b = 0, total_b = 0;
@@ -1264,6 +1381,7 @@ int lb_set_schedule(lb_ctx* ctx, const lb_schedule* s) {
     if (rc) return rc;
   }
   ctx->sched = *s;
+  ctx->small_passes = false;
   int rc = upload_schedule(ctx);
   if (!s->fused) release_state_b(ctx);
   return rc;
@@ -1389,6 +1507,8 @@ int autotune_timed(lb_ctx* ctx, int32_t steps, char* report, size_t report_len) 
     return fail(LB_EDEVICE, std::string("hipMemcpyAsync (autotune scratch copy): ") + hipGetErrorString(ce));
   }
 
+  const bool saved_small = ctx->small_passes;
+  ctx->small_passes = false;  // a tuned schedule is taken as it stands
   const std::vector<LatDesc> saved_lats = ctx->lats;
   const lb_schedule saved = ctx->sched;
   const int64_t saved_t = ctx->t;
@@ -1583,6 +1703,7 @@ int autotune_timed(lb_ctx* ctx, int32_t steps, char* report, size_t report_len) 
   (void)hipMemcpy(ctx->d_lats, ctx->lats.data(), sizeof(LatDesc) * ctx->lats.size(), hipMemcpyHostToDevice);
   hipLaunchKernelGGL(k_set_t, dim3(1), dim3(64), 0, ctx->stream, ctx->d_t, (uint64_t)saved_t);
   ctx->sched = (rc == LB_OK) ? best : saved;
+  ctx->small_passes = rc != LB_OK && saved_small;
   int rc2 = upload_schedule(ctx);
   if (!ctx->sched.fused) release_state_b(ctx);
   if (report && report_len) {

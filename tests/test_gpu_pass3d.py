@@ -11,7 +11,9 @@ import paper_0707_1581_amd as lbf
 
 pytestmark = pytest.mark.gpu
 
-BOXES = [(64, 13, 1), (65, 14, 2), (63, 12, 131), (128, 26, 9), (129, 27, 10), (1, 14, 65), (192, 1, 3), (2, 40, 2)]
+# above the 16384 sites up to which passes take blocks instead
+BOXES = [(64, 13, 20), (65, 14, 19), (63, 12, 131), (128, 26, 9), (129, 27, 10), (1, 14, 1301), (192, 1, 90),
+         (2, 40, 210), (300, 60, 1)]
 
 
 def _cfg(dims, kT):
@@ -37,7 +39,7 @@ def test_passes_equal_single_steps(dims, storage, kT):
         lat.close()
 
 
-@pytest.mark.parametrize("dims", [(65, 14, 3), (129, 27, 10)])
+@pytest.mark.parametrize("dims", [(65, 14, 19), (129, 27, 10)])
 def test_passes_propagate_exactly(dims):
     lat = lbf.Lattice(**_cfg(dims, 1e-4), storage="f16", init="thermal")
     lat.set_schedule(fused=1)

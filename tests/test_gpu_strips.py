@@ -14,7 +14,8 @@ import paper_0707_1581_amd as lbf
 
 pytestmark = pytest.mark.gpu
 
-BOXES = [(1, 42000), (2, 41003), (58, 41001), (59, 41007), (61, 20500), (117, 40963), (130, 17)]
+# above the 64 MB of state up to which passes take blocks instead, in every storage form
+BOXES = [(1, 3600007), (2, 1800011), (58, 62003), (59, 61007), (61, 59009), (117, 31013), (3600011, 1)]
 
 
 def _cfg(dims, kT=1e-4):
@@ -37,7 +38,7 @@ def test_strips_equal_single_steps(dims, storage):
     b.close()
 
 
-@pytest.mark.parametrize("dims", [(59, 41007), (130, 17)])
+@pytest.mark.parametrize("dims", [(59, 61007)])
 def test_strips_propagate_exactly(dims):
     lat = lbf.Lattice(**_cfg(dims), storage="bf16", init="thermal")
     lat.set_schedule(fused=1)
@@ -52,12 +53,12 @@ def test_strips_propagate_exactly(dims):
     lat.close()
 
 
-@pytest.mark.parametrize("dims", [(58, 41001), (3, 9)])
+@pytest.mark.parametrize("dims", [(58, 41001)])
 @pytest.mark.parametrize("steps", [4, 8])
 def test_strips_match_oracle(dims, steps):
     """Noiseless and noisy passes against the oracle at the first and last
-    columns and rows (whole small box, or a band of a tall one evolved alone:
-    its inner rows depend on nothing outside it for `steps` steps)."""
+    columns and rows (a band of the box evolved alone: its inner rows depend
+    on nothing outside it for `steps` steps)."""
     for kT in (0.0, 1e-3):
         cfg = _cfg(dims, kT)
         start = lbf.Lattice(**_cfg(dims, 1e-3), storage="f32", init="thermal")
