@@ -415,8 +415,16 @@ template <class M> struct Coef {
 template <class M, int S, class CF>
 __device__ __forceinline__ void collide(const CF& L, float d[M::Q], uint32_t site, uint32_t tlo, uint32_t thi) {
   constexpr int Q = M::Q, K0 = M::D + 1, NS = M::NSTRESS;
+  // the kinetic part stands before the noise: after it, all of d would be live
+  // across the noise beside mu (14 more registers, one wave less per SIMD)
   float mu[Q];
   M::template forward<false>(d, mu);
+  if (L.kinetic) {
+    M::template forward<true>(d, mu);
+  } else {
+#pragma unroll
+    for (int k = K0 + NS; k < Q; ++k) mu[k] = 0.0f;
+  }
 
   const float R = 36.0f + mu[0];
   const float iR = __builtin_amdgcn_rcpf(R);
@@ -451,7 +459,6 @@ __device__ __forceinline__ void collide(const CF& L, float d[M::Q], uint32_t sit
     nu[k] = __builtin_fmaf(L.ca[c], mu[k], __builtin_fmaf(L.cb[c], eq[k - K0], nu[k]));
   }
   if (L.kinetic) {
-    M::template forward<true>(d, mu);
 #pragma unroll
     for (int k = K0 + NS; k < Q; ++k) nu[k] = __builtin_fmaf(L.ca[ModeRep<M>::of(k)], mu[k], nu[k]);
   }
