@@ -271,7 +271,7 @@ typedef struct {
                         /* from even t, each launch reads the state once and   */
                         /* writes the state those steps later into a second    */
                         /* buffer that the library allocates                   */
-                        /* (the size of the state) and releases when the       */
+                        /* (the size of the state, or a sixteenth more) and releases when the       */
                         /* schedule goes back to 0 or the context is           */
                         /* destroyed.  Pairs of launches return the state to   */
                         /* the caller's buffer, so between calls it is always  */
@@ -329,8 +329,9 @@ int lb_autotune(lb_ctx* ctx, int32_t steps, char* report, size_t report_len);
  * laid out by lb_batch_pool_bytes / lb_batch_offset (one state buffer for
  * nrep = 1), each in the AA layout of step t0's parity (as the library left
  * it at step count t0); the caller owns it.  Launch shape: the default
- * schedule's block size, tilings and XCD remap, the streaming cache policy,
- * one launch per step over all lattices, no graph.
+ * schedule's block size, tilings and XCD remap, the streaming cache policy
+ * (every access cached for a lattice above 320 MB whose planes are not whole
+ * 128-byte lines), one launch per step over all lattices, no graph.
  * Memory: calls no allocating routine.  The descriptors, tile prefixes and
  * the step counter go into one static device array of the library (about
  * 23 KB, LB_NOALLOC_MAX_REPLICAS descriptors), which each GPU the library

@@ -205,25 +205,31 @@ void* rows_ptr(int lattice, int storage, int parity, bool res, int block, bool p
 
 // Fused passes of k steps per launch (D3Q19: k = 2; D2Q9: k = 2, 3 or 4) and
 // their propagation-only twins.  pull, own: the D3Q19 pass reads, writes
-// populations that are not streamed yet (between the passes of one call).
+// populations that are not streamed yet (between the passes of one call); nt:
+// the rows it writes are whole lines.
+template <int S, bool PROP, bool NT>
+void* pass3d_ptr(bool pull, bool own) {
+  if (pull) return own ? (void*)&k_pass3d<S, PROP, true, true, NT> : (void*)&k_pass3d<S, PROP, true, false, NT>;
+  return (void*)&k_pass3d<S, PROP, false, true, NT>;  // the first of two passes or more
+}
 template <int S, bool PROP>
-void* pass_ptr_s(int lattice, int k, bool pull, bool own) {
+void* pass_ptr_s(int lattice, int k, bool pull, bool own, bool nt) {
   if (lattice == LB_D2Q9)
     return k == 4 ? (void*)&k_strip2d<S, PROP, 4> : k == 3 ? (void*)&k_strip2d<S, PROP, 3> : (void*)&k_strip2d<S, PROP, 2>;
-  if (pull) return own ? (void*)&k_pass3d<S, PROP, true, true> : (void*)&k_pass3d<S, PROP, true, false>;
-  return (void*)&k_pass3d<S, PROP, false, true>;  // the first of two passes or more
+  return nt ? pass3d_ptr<S, PROP, true>(pull, own) : pass3d_ptr<S, PROP, false>(pull, own);
 }
 template <bool PROP>
-void* pass_ptr_p(int lattice, int storage, int k, bool pull, bool own) {
+void* pass_ptr_p(int lattice, int storage, int k, bool pull, bool own, bool nt) {
   switch (storage) {
-    case LB_F32: return pass_ptr_s<ST_F32, PROP>(lattice, k, pull, own);
-    case LB_F16: return pass_ptr_s<ST_F16, PROP>(lattice, k, pull, own);
-    case LB_BF16: return pass_ptr_s<ST_BF16, PROP>(lattice, k, pull, own);
+    case LB_F32: return pass_ptr_s<ST_F32, PROP>(lattice, k, pull, own, nt);
+    case LB_F16: return pass_ptr_s<ST_F16, PROP>(lattice, k, pull, own, nt);
+    case LB_BF16: return pass_ptr_s<ST_BF16, PROP>(lattice, k, pull, own, nt);
   }
   return nullptr;
 }
-void* pass_ptr(int lattice, int storage, int k, bool pull, bool own, bool prop) {
-  return prop ? pass_ptr_p<true>(lattice, storage, k, pull, own) : pass_ptr_p<false>(lattice, storage, k, pull, own);
+void* pass_ptr(int lattice, int storage, int k, bool pull, bool own, bool nt, bool prop) {
+  return prop ? pass_ptr_p<true>(lattice, storage, k, pull, own, nt)
+              : pass_ptr_p<false>(lattice, storage, k, pull, own, nt);
 }
 
 // Fused passes of small lattices, by the lanes of a workgroup.
@@ -420,6 +426,12 @@ uint32_t strip_rows(uint32_t across, uint32_t extent, uint32_t slots) {
   return (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, rows));
 }
 
+// Share of the sites of k_pass3d's tiles that lie in the box.
+double tile_fill(const lb_params& p) {
+  auto tiled = [](int32_t n, int t) { return (double)((n + t - 1) / t * t); };
+  return (double)p.nx * p.ny / (tiled(p.nx, P3_TX) * tiled(p.ny, P3_TY));
+}
+
 // Whether the passes over a lattice are k_block's: D2Q9 of up to 64 MB (1024^2
 // fp32, 38 MB: 10.6 us per step, strips 11.7; 2048^2: 34.3 and 32.8) and D3Q19
 // of up to 16384 sites (beyond, the AA steps are as fast: 24^3 fp32 4.0 against
@@ -508,7 +520,7 @@ int plan_passes(lb_ctx* c) {
     lb_ctx::PassPlan& p = c->plans[k];
     p.threads = c->lattice == LB_D2Q9 ? 64 * S2_WAVES : P3_THREADS;
     int per_cu = 0;
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pass_ptr(c->lattice, c->storage, k, true, true, false), p.threads, 0));
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pass_ptr(c->lattice, c->storage, k, true, true, true, false), p.threads, 0));
     const uint32_t slots = (uint32_t)std::max(1, cus * per_cu);  // workgroups resident at a time
     if (c->lattice == LB_D2Q9) {
       StripGeom& g = p.strip;
@@ -600,11 +612,28 @@ bool fused_eligible(const lb_ctx* c) {
   return slice < (1ull << 32);
 }
 
-// The fused schedule's second buffer: allocated once, the size of the state,
-// if the device has room for it beside a margin of 1 GiB.
+// The fused schedule's second buffer holds the q populations of an x-row side
+// by side (see k_pass3d), where a slice of it (a z-plane, a D2Q9 row) fits the
+// range of a buffer descriptor; else whole planes, as the state.  D3Q19 rows
+// start on 128-byte lines where that costs at most a sixteenth more.
+size_t second_pitch(const lb_params& p) {
+  const size_t row = (size_t)p.nx * elem_size(p.storage), up = (row + 127) & ~(size_t)127;
+  return p.lattice == LB_D3Q19 && (up - row) * 16 <= row ? up : row;
+}
+bool second_rows(const lb_params& p) {
+  const size_t rows = p.lattice == LB_D2Q9 ? 1 : (size_t)p.ny;
+  return (size_t)q_of(p.lattice) * rows * second_pitch(p) < (1ull << 32);
+}
+size_t second_bytes(const lb_params& p) {
+  const size_t q = (size_t)q_of(p.lattice);
+  return second_rows(p) ? q * second_pitch(p) * p.ny * p.nz : q * sites_of(p) * elem_size(p.storage);
+}
+
+// The second buffer is allocated once, if the device has room for it beside a
+// margin of 1 GiB.
 int ensure_state_b(lb_ctx* c) {
   if (c->d_state_b) return LB_OK;
-  const size_t bytes = (size_t)q_of(c->lattice) * sites_of(c->reps[0]) * elem_size(c->storage);
+  const size_t bytes = second_bytes(c->reps[0]);
   size_t free_b = 0, total_b = 0;
   HIP_TRY(hipMemGetInfo(&free_b, &total_b));
   if (free_b < bytes + (1ull << 30))
@@ -692,11 +721,11 @@ lb_ctx::PassArgs pass_args(const lb_ctx* c, uint32_t t_off, const std::vector<in
   const PassSide A{L.base, L.plane * elem_size(c->storage), slice, row, slice};
   PassSide B = A;
   B.base = (uint64_t)(uintptr_t)(c->sched.fused ? c->d_state_b : c->d_small_b);
-  const uint32_t q = (uint32_t)q_of(c->lattice);
-  if ((uint64_t)q * slice < (1ull << 32)) {
-    B.plane = row;
-    B.row = q * row;
-    B.slice = B.span = q * slice;
+  if (second_rows(c->reps[0])) {
+    const uint32_t pitch = (uint32_t)second_pitch(c->reps[0]), q = (uint32_t)q_of(c->lattice);
+    B.plane = pitch;
+    B.row = q * pitch;
+    B.slice = B.span = c->lattice == LB_D2Q9 ? B.row : B.row * L.ny;
   }
   const bool to_b = (n & 1) == 0;
   for (size_t j = 0; j < n; ++j) t_off += (uint32_t)ks[j];
@@ -705,7 +734,8 @@ lb_ctx::PassArgs pass_args(const lb_ctx* c, uint32_t t_off, const std::vector<in
   bg.to = to_b ? B.base : A.base;
   return {c->d_lats, to_b ? A : B, to_b ? B : A, c->d_t, t_off, p.tiles, p.strip, bg, t_off,
           c->blocks ? block_ptr(c->lattice, c->storage, p.threads, prop)
-                    : pass_ptr(c->lattice, c->storage, ks[n], n > 0, n + 1 < ks.size(), prop)};
+                    : pass_ptr(c->lattice, c->storage, ks[n], n > 0, n + 1 < ks.size(),
+                               (to_b ? (uint32_t)B.plane : row) % 128 == 0, prop)};
 }
 
 int launch_pass(lb_ctx* c, uint32_t t_off, const std::vector<int>& ks, size_t n, bool prop) {
@@ -884,26 +914,26 @@ int init_lattice(lb_ctx* c, int idx, int kind, const float* d_fields, int parity
 
 // Launch shape of the AA steps: block size, tilings and XCD remap, from
 // measurements on MI355X.
-// One lattice of more than 320 MB streams through HBM in long rows: fp32 runs
-// the even step row-tiled and the odd step flat, both without XCD remapping;
-// the 16-bit forms run the even step flat and the odd step row-tiled, with
-// XCD groups of 8 consecutive tiles on D3Q19 and no remapping on D2Q9 (groups
-// of 8 made the D2Q9 bf16 step 10% slower).  So do smaller 16-bit lattices
-// whose rows fill the row tiles (256 x 256 x 24 fp16: 23.0 us per step, flat
-// 24.3; 4096^2 bf16 114 against 118), D2Q9 with groups of 8 up to 128 MB (1024^2
-// bf16 10.6 against 12.0 us).
-// Other smaller lattices and batches run flat: their rows are seldom a multiple of
-// a row tile's 256 lanes, and the idle lanes cost more than the per-lane
-// division the flat tiling adds (96-replica fp16 ensemble 501 against 405 us
-// per step, fp32 748 against 711; 128^3 fp16 36.9 against 28.5; 64^3 fp32
-// 11.6 against 7.5; 97 x 131 x 75 bf16 19.1 against 17.3; 1000^2 fp32 19.2
-// against 13.6), with XCD groups of 8 so that neighbouring tiles share an L2.
+// Tiles are flat, in XCD groups of 8 so that neighbouring ones share an L2:
+// rows are seldom a multiple of a row tile's 256 lanes, and the idle lanes cost
+// more than the per-lane division the flat tiling adds (96-replica fp16 ensemble
+// 501 against 405 us per step, fp32 748 against 711; 128^3 fp16 36.9 against
+// 28.5; 64^3 fp32 11.6 against 7.5; 300^3 fp16 512 against 404).  Rows that fill
+// the row tiles of one lattice keep them: fp32 above 320 MB on the even step,
+// without XCD groups (512 x 512 x 300 2141 against 2181), 16 bits on the odd step
+// (256 x 256 x 24 fp16 23.0 against 24.3), with XCD groups on D3Q19 and on D2Q9
+// of up to 128 MB (1024^2 bf16 10.6 against 12.0, but 16384^2 10% slower).
+// A lattice whose planes are not whole 128-byte lines caches every access: a
+// tile ends inside lines of most planes, and streaming the parts costs far more
+// than caching them (441 x 318 x 225 fp16 654 against 515 us, fp32 1085 against
+// 942; 511 x 513 x 300 fp16 1587 against 1259).
 // The smallest take smaller workgroups, so that more CUs work on them (16^3
 // fp32 4.3 us with 256 lanes, 3.9 with 64; 32^3 4.5 and 4.3 with 128).
 struct AaShape {
   int block;
   int remap[2];
   int tiling[2];
+  bool cached;  // every access
 };
 AaShape aa_shape(const lb_params* reps, size_t nrep) {
   uint64_t sites = 0, bytes = 0;
@@ -911,13 +941,16 @@ AaShape aa_shape(const lb_params* reps, size_t nrep) {
     sites += sites_of(reps[r]);
     bytes += (uint64_t)q_of(reps[r].lattice) * sites_of(reps[r]) * elem_size(reps[r].storage);
   }
-  const bool full_rows = nrep == 1 && reps[0].nx % 256 == 0 && reps[0].storage != LB_F32;
-  if (nrep > 1 || (bytes <= 320000000ull && !full_rows))
-    return {sites <= 16384 ? 64 : sites <= 65536 ? 128 : 256, {8, 8}, {0, 0}};
-  AaShape s{256, {0, 0}, {0, 0}};
-  if (bytes <= 128000000ull) s.remap[0] = s.remap[1] = 8;
-  if (reps[0].storage != LB_F32 && reps[0].lattice == LB_D3Q19) s.remap[0] = s.remap[1] = 8;
-  if (!is_wide(reps[0])) s.tiling[reps[0].storage == LB_F32 ? 0 : 1] = 1;
+  const bool one = nrep == 1, f32 = reps[0].storage == LB_F32, wide = one && is_wide(reps[0]);
+  const bool large = one && bytes > 320000000ull;
+  const int block = sites <= 16384 ? 64 : sites <= 65536 ? 128 : 256;
+  AaShape s{block, {8, 8}, {0, 0}, false};
+  if (one && reps[0].nx % 256 == 0 && (large || !f32)) {
+    s.block = 256;
+    if (!wide) s.tiling[f32 ? 0 : 1] = 1;
+    if (f32 || (reps[0].lattice == LB_D2Q9 && bytes > 128000000ull)) s.remap[0] = s.remap[1] = 0;
+  }
+  s.cached = large && !wide && sites * elem_size(reps[0].storage) % 128 != 0;
   return s;
 }
 
@@ -931,7 +964,7 @@ AaShape aa_shape(const lb_params* reps, size_t nrep) {
 // workload.
 int default_schedule(lb_ctx* c) {
   const AaShape sh = aa_shape(c->reps.data(), c->reps.size());
-  c->sched = lb_schedule{sh.block, 0, 16, {sh.remap[0], sh.remap[1]}, {sh.tiling[0], sh.tiling[1]}, 0, 0, 0};
+  c->sched = lb_schedule{sh.block, 0, 16, {sh.remap[0], sh.remap[1]}, {sh.tiling[0], sh.tiling[1]}, sh.cached, 0, 0};
   uint64_t total = 0, largest = 0;
   for (const lb_params& p : c->reps) {
     const uint64_t b = (uint64_t)q_of(p.lattice) * sites_of(p) * elem_size(p.storage);
@@ -955,12 +988,13 @@ int default_schedule(lb_ctx* c) {
   // between 724^2 (19 MB, AA 6% faster) and 1024^2 (38 MB, fused 7% faster).
   // 16-bit D2Q9 state takes them above the resident band (16384^2 bf16: 1.55
   // against 1.84 ms per step; 4096^2, inside it, 111 against 118 us; 2048^2 36
-  // against 31).  So does 16-bit D3Q19 state without noise (512^3 fp16 1.45
-  // against 1.96 ms; 256^3 192 against 208 us); with noise the collisions bound
+  // against 31).  So does 16-bit D3Q19 state without noise on boxes that fill the
+  // tiles (512^3 fp16 1.45 against 1.96 ms; 256^3 192 against 208 us; 400 x 300 x
+  // 350, 86% filled, 636 against 655, 200 x 234 x 342, 76%, 8% slower); with noise the collisions bound
   // the pass (512^3 fp16 1.99 against 1.85 ms) and it keeps one step per launch.
   const bool d2 = c->lattice == LB_D2Q9, f32 = c->storage == LB_F32;
   const uint64_t fused_above = f32 ? (d2 ? 32 * MIB : 256 * MIB) : 320 * MB;
-  const bool pays = d2 || f32 || c->reps[0].kT == 0.0;
+  const bool pays = d2 || f32 || (c->reps[0].kT == 0.0 && tile_fill(c->reps[0]) >= 0.9);
   c->small_passes = c->d_small_b != nullptr;
   if (pays && fused_eligible(c) && total > fused_above) {
     const std::string keep = g_last_error;
@@ -1746,7 +1780,7 @@ int lb_step_noalloc(const lb_params* reps, int32_t nrep, void* d_pool, void* hip
   uint64_t* d_t = reinterpret_cast<uint64_t*>(base + NA_OFF_T);
   hipStream_t st = (hipStream_t)hip_stream;
 
-  // the library's default launch shape, streaming cache policy, one launch per step
+  // the library's default launch shape, one launch per step
   const AaShape shape = aa_shape(reps, (size_t)nrep);
   const uint32_t BLOCK = (uint32_t)shape.block;
   const int storage = reps[0].storage, lattice = reps[0].lattice;
@@ -1788,8 +1822,8 @@ int lb_step_noalloc(const lb_params* reps, int32_t nrep, void* d_pool, void* hip
     for (int64_t s = 0; s < m; ++s) {
       const int parity = (int)((t0 + s0 + s) & 1);
       const bool rows = shape.tiling[parity] != 0;
-      void* fn = rows ? rows_ptr(lattice, storage, parity, false, (int)BLOCK, false)
-                      : step_ptr(lattice, storage, parity, wide, false, (int)BLOCK, false);
+      void* fn = rows ? rows_ptr(lattice, storage, parity, shape.cached, (int)BLOCK, false)
+                      : step_ptr(lattice, storage, parity, wide, shape.cached, (int)BLOCK, false);
       const LatDesc* lats = d_lats;
       const uint32_t* blk = rows ? d_blk_rows : d_blk;
       uint32_t rm = (uint32_t)shape.remap[parity];

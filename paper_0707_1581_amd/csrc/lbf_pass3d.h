@@ -22,7 +22,10 @@
 // Layouts.  Between the passes of one call the state need not be streamed: all
 // but the last pass store the second step's populations at their own site
 // (whole aligned rows, past the caches), and all but the first pull them from
-// r - c_i.  The first pass reads and the last writes the even AA layout.  The
+// r - c_i.  NT: the destination's rows are whole 128-byte lines; where they are
+// not, a tile's row ends inside lines, and streaming the parts costs more than
+// caching them (with the pitch of the second buffer, 441 x 318 x 225 fp32 takes
+// 651 us per step instead of 784).  The first pass reads and the last writes the even AA layout.  The
 // second buffer holds the 19 populations of an x-row side by side: with planes
 // on both sides a workgroup would have 38 pages or more in use at a time, more
 // than the CU's address translation cache holds (22e6 misses a pass at 512^3,
@@ -73,7 +76,7 @@ struct PassGeom {
   uint32_t ntx, nty, tx, ty, len;
 };
 
-template <int S, bool PROP, bool PULL, bool OWN>
+template <int S, bool PROP, bool PULL, bool OWN, bool NT>
 __global__ void __launch_bounds__(P3_THREADS)
 k_pass3d(const LatDesc* __restrict__ src, PassSide from, PassSide to, const uint64_t* __restrict__ d_t,
          uint32_t t_off, PassGeom g) {
@@ -154,8 +157,8 @@ k_pass3d(const LatDesc* __restrict__ src, PassSide from, PassSide to, const uint
       const uint64_t zo = cz > 0 ? op : (cz < 0 ? om : o0);
       T o;
       if constexpr (PROP) o = h[j]; else o = C::enc(h[j]);
-      // x-shifted rows share lines with the neighbouring tiles: cached; the others stream
-      Raw<T>::template st<pol(cx == 0)>(span_rsrc(a + zo, to.span), on ? xd * ES + yd * to.row : NOWHERE, o);
+      // rows that share lines with the neighbouring tiles are cached, whole lines stream
+      Raw<T>::template st<pol(NT && cx == 0)>(span_rsrc(a + zo, to.span), on ? xd * ES + yd * to.row : NOWHERE, o);
       a += to.plane;
     });
   };
