@@ -333,7 +333,7 @@ int lb_autotune(lb_ctx* ctx, int32_t steps, char* report, size_t report_len);
  * (every access cached for a lattice above 320 MB whose planes are not whole
  * 128-byte lines), one launch per step over all lattices, no graph.
  * Memory: calls no allocating routine.  The descriptors, tile prefixes and
- * the step counter go into one static device array of the library (about
+ * the step count go into one static device array of the library (about
  * 23 KB, LB_NOALLOC_MAX_REPLICAS descriptors), which each GPU the library
  * runs on holds until the process ends and which keeps the last call's
  * contents; every call rewrites what it uses, in stream order, before its

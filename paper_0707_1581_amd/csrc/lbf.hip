@@ -306,9 +306,9 @@ struct lb_ctx {
   bool wide = false;
   std::vector<lb_params> reps;  // one per lattice (1 for a single lattice)
   std::vector<uint64_t> offsets;
-  int64_t t = 0;                // host mirror of *d_t
+  int64_t t = 0;                // host mirror of d_t[t & 1]
 
-  // device metadata: [d_t (8 B) | result (5 doubles) | pad] [partials] [lats] [lats in tile order] [blk]
+  // device metadata: [d_t (2 slots) | result (5 doubles) | pad] [partials] [lats] [lats in tile order] [blk]
   char* d_meta = nullptr;
   uint64_t* d_t = nullptr;
   double* d_result = nullptr;
@@ -338,14 +338,23 @@ struct lb_ctx {
     const uint32_t* blk;
     uint32_t nlat;
     uint32_t remap;
-    const uint64_t* d_t;
-    uint32_t t_off;
+    Clock clock;
   };
   std::vector<StepArgs> graph_args;
-  struct AdvArgs {
-    uint64_t* d_t;
+
+  // A run is a sequence of launches that together take n steps from t; tick(s)
+  // is the clock of its next launch, which is at its step s.
+  struct Run {
+    uint64_t *at, *other;  // the slots of t and of t + 1
     uint64_t n;
-  } adv_args;
+    int launches;
+    Run(uint64_t* d_t, int64_t t, int64_t steps) : at(d_t + (t & 1)), other(d_t + (1 - (t & 1))), n((uint64_t)steps), launches(0) {}
+    Clock tick(uint64_t s) {
+      ++launches;
+      if (launches == 1) return {at, s, other, n};
+      return {other, s - n, launches == 2 && !(n & 1) ? at : nullptr, 0};
+    }
+  };
 
   // fused schedule: the second state buffer (library-owned), the launches of
   // its passes and the most steps a pass takes
@@ -369,17 +378,15 @@ struct lb_ctx {
   struct PassArgs {
     const LatDesc* src;
     PassSide from, to;
-    const uint64_t* d_t;
-    uint32_t t_off;
+    Clock clock;
     PassGeom tiles;
     StripGeom strip;
     BlockGeom block;
-    uint64_t t_off64;
     void* fn;
     // the kernel's arguments in order
     std::vector<void*> list(int lattice) {
-      if (block.steps) return {&src, &d_t, &t_off64, &block};
-      return {&src, &from, &to, &d_t, &t_off, lattice == LB_D2Q9 ? (void*)&strip : (void*)&tiles};
+      if (block.steps) return {&src, &clock, &block};
+      return {&src, &from, &to, &clock, lattice == LB_D2Q9 ? (void*)&strip : (void*)&tiles};
     }
   };
   std::vector<PassArgs> graph_pass_args;
@@ -675,14 +682,14 @@ StepLaunch step_launch(const lb_ctx* c, int parity, size_t g, bool prop = false)
           c->d_tile_lats + G.first, c->d_blk + G.first, G.count};
 }
 
-// One step of every group.  prop: the propagation-only kernels of the same
-// schedule instead.
-int launch_step(lb_ctx* c, uint32_t t_off, int parity, bool prop = false) {
+// One step of every group, step s of a run.  prop: the propagation-only kernels
+// of the same schedule instead.
+int launch_step(lb_ctx* c, lb_ctx::Run& run, uint64_t s, int parity, bool prop = false) {
   for (size_t g = 0; g < c->groups.size(); ++g) {
     const StepLaunch sl = step_launch(c, parity, g, prop);
     if (!sl.fn) return fail(LB_EINVAL, "no step kernel for this schedule");
-    lb_ctx::StepArgs a{sl.lats, sl.blk, sl.nlat, (uint32_t)c->sched.xcd_remap[parity], c->d_t, t_off};
-    void* args[] = {&a.lats, &a.blk, &a.nlat, &a.remap, &a.d_t, &a.t_off};
+    lb_ctx::StepArgs a{sl.lats, sl.blk, sl.nlat, (uint32_t)c->sched.xcd_remap[parity], run.tick(s)};
+    void* args[] = {&a.lats, &a.blk, &a.nlat, &a.remap, &a.clock};
     HIP_TRY(hipLaunchKernel(sl.fn, dim3(sl.grid), dim3(sl.block), args, 0, c->stream));
   }
   return LB_OK;
@@ -709,11 +716,11 @@ std::vector<int> pass_steps(const lb_ctx* c, int64_t m) {
   return ks;
 }
 
-// Pass n of ks, the first of which starts at even t + t_off: state buffer ->
-// second buffer (n even) or back.  The second buffer holds the q populations of
+// Pass n of ks, step s of a run that starts at an even t: state buffer -> second
+// buffer (n even) or back.  The second buffer holds the q populations of
 // an x-row side by side (see k_pass3d) where a slice of it (a z-plane, a D2Q9
 // row) fits the range of a buffer descriptor.
-lb_ctx::PassArgs pass_args(const lb_ctx* c, uint32_t t_off, const std::vector<int>& ks, size_t n, bool prop) {
+lb_ctx::PassArgs pass_args(const lb_ctx* c, const Clock& clock, const std::vector<int>& ks, size_t n, bool prop) {
   const LatDesc& L = c->lats[0];
   const lb_ctx::PassPlan& p = c->plans[ks[n]];
   const uint32_t row = L.nx * (uint32_t)elem_size(c->storage);
@@ -728,32 +735,25 @@ lb_ctx::PassArgs pass_args(const lb_ctx* c, uint32_t t_off, const std::vector<in
     B.slice = B.span = c->lattice == LB_D2Q9 ? B.row : B.row * L.ny;
   }
   const bool to_b = (n & 1) == 0;
-  for (size_t j = 0; j < n; ++j) t_off += (uint32_t)ks[j];
   BlockGeom bg = p.block;
   bg.from = to_b ? A.base : B.base;
   bg.to = to_b ? B.base : A.base;
-  return {c->d_lats, to_b ? A : B, to_b ? B : A, c->d_t, t_off, p.tiles, p.strip, bg, t_off,
+  return {c->d_lats, to_b ? A : B, to_b ? B : A, clock, p.tiles, p.strip, bg,
           c->blocks ? block_ptr(c->lattice, c->storage, p.threads, prop)
                     : pass_ptr(c->lattice, c->storage, ks[n], n > 0, n + 1 < ks.size(),
                                (to_b ? (uint32_t)B.plane : row) % 128 == 0, prop)};
 }
 
-int launch_pass(lb_ctx* c, uint32_t t_off, const std::vector<int>& ks, size_t n, bool prop) {
-  lb_ctx::PassArgs a = pass_args(c, t_off, ks, n, prop);
+int launch_pass(lb_ctx* c, const Clock& clock, const std::vector<int>& ks, size_t n, bool prop) {
+  lb_ctx::PassArgs a = pass_args(c, clock, ks, n, prop);
   const lb_ctx::PassPlan& p = c->plans[ks[n]];
   HIP_TRY(hipLaunchKernel(a.fn, p.grid, dim3(p.threads), a.list(c->lattice).data(), 0, c->stream));
   return LB_OK;
 }
 
-int launch_advance(lb_ctx* c, uint64_t n) {
-  hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, c->stream, c->d_t, n);
-  HIP_TRY(hipGetLastError());
-  return LB_OK;
-}
-
 // A chain of graph_chunk steps of each group in turn (all steps of one group
 // before the next, so a group whose state fits in the Infinity Cache stays
-// there), then the counter advance.  Under the fused schedule (one lattice)
+// there), as one run from an even t.  Under the fused schedule (one lattice)
 // the chain is pairs of fused passes, out to the second buffer and back, and
 // AA steps for the rest of the chunk.
 int build_graph(lb_ctx* c) {
@@ -779,9 +779,12 @@ int build_graph(lb_ctx* c) {
     prev = node;
     return LB_OK;
   };
+  lb_ctx::Run run(c->d_t, 0, K);
+  uint64_t at = 0;
   for (size_t n = 0; n < ks.size(); ++n) {
     lb_ctx::PassArgs& a = c->graph_pass_args[n];
-    a = pass_args(c, 0, ks, n, false);
+    a = pass_args(c, run.tick(at), ks, n, false);
+    at += (uint64_t)ks[n];
     const lb_ctx::PassPlan& p = c->plans[ks[n]];
     int rc = add_node(a.fn, p.grid, p.threads, a.list(c->lattice).data());
     if (rc) return rc;
@@ -792,39 +795,34 @@ int build_graph(lb_ctx* c) {
     const int s = covered + (int)(n % K1);
     const StepLaunch sl = step_launch(c, s & 1, g);
     if (!sl.fn) return fail(LB_EINVAL, "no step kernel for this schedule");
-    c->graph_args[n] = {sl.lats, sl.blk, sl.nlat, (uint32_t)c->sched.xcd_remap[s & 1], c->d_t, (uint32_t)s};
+    c->graph_args[n] = {sl.lats, sl.blk, sl.nlat, (uint32_t)c->sched.xcd_remap[s & 1], run.tick((uint64_t)s)};
     lb_ctx::StepArgs& a = c->graph_args[n];
-    void* args[] = {&a.lats, &a.blk, &a.nlat, &a.remap, &a.d_t, &a.t_off};
+    void* args[] = {&a.lats, &a.blk, &a.nlat, &a.remap, &a.clock};
     int rc = add_node(sl.fn, dim3(sl.grid), sl.block, args);
     if (rc) return rc;
   }
-  c->adv_args = {c->d_t, (uint64_t)K};
-  void* aargs[] = {&c->adv_args.d_t, &c->adv_args.n};
-  int rc = add_node((void*)&k_advance, dim3(1), 64, aargs);
-  if (rc) return rc;
   HIP_TRY(hipGraphInstantiate(&c->graph_exec, c->graph, nullptr, nullptr, 0));
   return LB_OK;
 }
 
-// m steps launched one by one (prop: the propagation-only kernels), then the
-// counter advance.  Under the fused schedule, from even t, pairs of fused
-// passes (out to the second buffer and back) cover all but the last steps.
+// m steps launched one by one (prop: the propagation-only kernels) as one run.
+// Where passes are on, from even t, pairs of fused passes (out to the second
+// buffer and back) cover all but the last steps.
 int direct_steps(lb_ctx* c, int64_t m, bool prop = false) {
   int64_t s = 0;
+  lb_ctx::Run run(c->d_t, c->t, m);
   if (c->passes(prop) && !(c->t & 1)) {
     const std::vector<int> ks = pass_steps(c, m);
     for (size_t n = 0; n < ks.size(); ++n) {
-      int rc = launch_pass(c, 0, ks, n, prop);
+      int rc = launch_pass(c, run.tick((uint64_t)s), ks, n, prop);
       if (rc) return rc;
       s += ks[n];
     }
   }
   for (; s < m; ++s) {
-    int rc = launch_step(c, (uint32_t)s, (int)((c->t + s) & 1), prop);
+    int rc = launch_step(c, run, (uint64_t)s, (int)((c->t + s) & 1), prop);
     if (rc) return rc;
   }
-  int rc = launch_advance(c, (uint64_t)m);
-  if (rc) return rc;
   c->t += m;
   return LB_OK;
 }
@@ -857,7 +855,7 @@ int advance(lb_ctx* c, int64_t n) {
       n -= K;
     }
   }
-  while (n > 0) {  // the device counter advances every K steps, as in a replay
+  while (n > 0) {
     const int64_t m = std::min<int64_t>(n, long_passes ? 1024 : K);
     int rc = direct_steps(c, m);
     if (rc) return rc;
@@ -1036,10 +1034,10 @@ int gather(lb_ctx* c, int what, float* d_out) {
 
 // ---------------------------------------------------------------- steps without allocation
 // lb_step_noalloc keeps what a context would hold in device memory (lattice
-// descriptors, tile prefixes, the step counter) in one file-scope device
-// array instead.  Host code never uses the array's name as an address: its
-// device address comes from hipGetSymbolAddress, once per device.
-constexpr size_t NA_OFF_T = 0;                                          // uint64 step counter
+// descriptors, tile prefixes, the step count) in one file-scope device array
+// instead.  Host code never uses the array's name as an address: its device
+// address comes from hipGetSymbolAddress, once per device.
+constexpr size_t NA_OFF_T = 0;                                          // uint64 step count of the call
 constexpr size_t NA_OFF_BLK = 256;                                      // flat tile prefix
 constexpr size_t NA_OFF_BLKR = NA_OFF_BLK + 4 * (LB_NOALLOC_MAX_REPLICAS + 1 + 63);  // row tile prefix
 constexpr size_t NA_OFF_DESC = (NA_OFF_BLKR + 4 * (LB_NOALLOC_MAX_REPLICAS + 1) + 255) & ~(size_t)255;
@@ -1144,7 +1142,7 @@ int lb_init(const lb_params* p, void* d_state, void* hip_stream, int32_t init_ki
     free_ctx(c);
     return rc;
   }
-  hipLaunchKernelGGL(k_set_t, dim3(1), dim3(64), 0, c->stream, c->d_t, (uint64_t)t0);
+  hipLaunchKernelGGL(k_set_t, dim3(1), dim3(64), 0, c->stream, c->d_t + (t0 & 1), (uint64_t)t0);
   e = hipGetLastError();
   if (e != hipSuccess) {
     free_ctx(c);
@@ -1343,7 +1341,7 @@ int lb_batch_init(const lb_params* reps, int32_t nrep, void* d_pool, void* hip_s
     free_ctx(c);
     return rc;
   }
-  hipLaunchKernelGGL(k_set_t, dim3(1), dim3(64), 0, c->stream, c->d_t, (uint64_t)t0);
+  hipLaunchKernelGGL(k_set_t, dim3(1), dim3(64), 0, c->stream, c->d_t + (t0 & 1), (uint64_t)t0);
   e = hipGetLastError();
   if (e != hipSuccess) {
     free_ctx(c);
@@ -1569,9 +1567,9 @@ int autotune_timed(lb_ctx* ctx, int32_t steps, char* report, size_t report_len) 
     for (int k = 0; k < 2 * steps && r == LB_OK; ++k) {
       const int parity = (int)(ctx->t & 1);
       if (hipEventRecord(ev[0], ctx->stream) != hipSuccess) return fail(LB_EDEVICE, "hipEventRecord");
-      if ((r = launch_step(ctx, 0, parity))) break;
+      lb_ctx::Run run(ctx->d_t, ctx->t, 1);
+      if ((r = launch_step(ctx, run, 0, parity))) break;
       if (hipEventRecord(ev[1], ctx->stream) != hipSuccess) return fail(LB_EDEVICE, "hipEventRecord");
-      if ((r = launch_advance(ctx, 1))) break;
       ctx->t += 1;
       if (hipEventSynchronize(ev[1]) != hipSuccess) return fail(LB_EDEVICE, "hipEventSynchronize");
       float ms = 0.f;
@@ -1735,7 +1733,7 @@ int autotune_timed(lb_ctx* ctx, int32_t steps, char* report, size_t report_len) 
   ctx->lats = saved_lats;
   ctx->t = saved_t;
   (void)hipMemcpy(ctx->d_lats, ctx->lats.data(), sizeof(LatDesc) * ctx->lats.size(), hipMemcpyHostToDevice);
-  hipLaunchKernelGGL(k_set_t, dim3(1), dim3(64), 0, ctx->stream, ctx->d_t, (uint64_t)saved_t);
+  hipLaunchKernelGGL(k_set_t, dim3(1), dim3(64), 0, ctx->stream, ctx->d_t + (saved_t & 1), (uint64_t)saved_t);
   ctx->sched = (rc == LB_OK) ? best : saved;
   ctx->small_passes = rc != LB_OK && saved_small;
   int rc2 = upload_schedule(ctx);
@@ -1786,7 +1784,7 @@ int lb_step_noalloc(const lb_params* reps, int32_t nrep, void* d_pool, void* hip
   const int storage = reps[0].storage, lattice = reps[0].lattice;
   const bool wide = is_wide(reps[0]);
 
-  // descriptors, in chunks passed by value, then the tile prefixes and the step counter
+  // descriptors, in chunks passed by value, then the tile prefixes and the step count
   NaMeta meta{};
   uint64_t off = 0, acc = 0, acc_rows = 0;
   for (int r0 = 0; r0 < nrep; r0 += NA_CHUNK) {
@@ -1815,26 +1813,19 @@ int lb_step_noalloc(const lb_params* reps, int32_t nrep, void* d_pool, void* hip
   hipLaunchKernelGGL(k_noalloc_meta, dim3(1), dim3(64), 0, st, meta, d_blk, d_blk_rows, d_t);
   HIP_TRY(hipGetLastError());
 
-  // the steps, in runs of 16 launches between counter advances
   const uint32_t nlat = (uint32_t)nrep;
-  for (int64_t s0 = 0; s0 < nsteps; s0 += 16) {
-    const int64_t m = std::min<int64_t>(16, nsteps - s0);
-    for (int64_t s = 0; s < m; ++s) {
-      const int parity = (int)((t0 + s0 + s) & 1);
-      const bool rows = shape.tiling[parity] != 0;
-      void* fn = rows ? rows_ptr(lattice, storage, parity, shape.cached, (int)BLOCK, false)
-                      : step_ptr(lattice, storage, parity, wide, shape.cached, (int)BLOCK, false);
-      const LatDesc* lats = d_lats;
-      const uint32_t* blk = rows ? d_blk_rows : d_blk;
-      uint32_t rm = (uint32_t)shape.remap[parity];
-      const uint64_t* dt = d_t;
-      uint32_t t_off = (uint32_t)s;
-      uint32_t nl = nlat;
-      void* args[] = {&lats, &blk, &nl, &rm, &dt, &t_off};
-      HIP_TRY(hipLaunchKernel(fn, dim3((uint32_t)(rows ? acc_rows : acc)), dim3(BLOCK), args, 0, st));
-    }
-    hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, st, d_t, (uint64_t)m);
-    HIP_TRY(hipGetLastError());
+  for (int64_t s = 0; s < nsteps; ++s) {
+    const int parity = (int)((t0 + s) & 1);
+    const bool rows = shape.tiling[parity] != 0;
+    void* fn = rows ? rows_ptr(lattice, storage, parity, shape.cached, (int)BLOCK, false)
+                    : step_ptr(lattice, storage, parity, wide, shape.cached, (int)BLOCK, false);
+    const LatDesc* lats = d_lats;
+    const uint32_t* blk = rows ? d_blk_rows : d_blk;
+    uint32_t rm = (uint32_t)shape.remap[parity];
+    Clock clock{d_t, (uint64_t)s, nullptr, 0};
+    uint32_t nl = nlat;
+    void* args[] = {&lats, &blk, &nl, &rm, &clock};
+    HIP_TRY(hipLaunchKernel(fn, dim3((uint32_t)(rows ? acc_rows : acc)), dim3(BLOCK), args, 0, st));
   }
   return LB_OK;
 }

@@ -36,7 +36,7 @@ template <class M> struct BlockSlot {
 
 template <class M, int S, bool PROP, int NL>
 __global__ void __launch_bounds__(NL)
-k_block(const LatDesc* __restrict__ src, const uint64_t* __restrict__ d_t, uint64_t t_off, BlockGeom g) {
+k_block(const LatDesc* __restrict__ src, Clock ck, BlockGeom g) {
   using C = Codec<S>;
   using T = typename C::T;
   constexpr int Q = M::Q;
@@ -76,7 +76,7 @@ k_block(const LatDesc* __restrict__ src, const uint64_t* __restrict__ d_t, uint6
   T own[Q];
 #pragma unroll
   for (int i = 0; i < Q; ++i) own[i] = Raw<T>::template ld<0>(in, site * ES, (uint32_t)i * pbytes);
-  const uint64_t t = (d_t ? *d_t : 0u) + t_off;
+  const uint64_t t = ck.read();
 
   // distance of this lane from the edge of the block with its halo: its site
   // is right up to the step of that number
@@ -130,6 +130,7 @@ k_block(const LatDesc* __restrict__ src, const uint64_t* __restrict__ d_t, uint6
                        (M::CZ[i] > 0 ? zp : (M::CZ[i] < 0 ? zm : z0));
     Raw<T>::template st<0>(out, mine ? s * ES : NOWHERE, own[i], (uint32_t)i * pbytes);
   }
+  ck.tick(t);
 }
 
 }  // namespace lbf

@@ -76,6 +76,28 @@ __device__ __forceinline__ uint32_t fastdiv(uint32_t n, uint32_t m, uint32_t s1,
   return (t + ((n - t) >> s1)) >> s2;
 }
 
+// ---------------------------------------------------------------- step counter
+// The step count of a launch: *now + off.  The counter lives on
+// the device, so that a replayed graph goes on from where it is.  It has two
+// slots, so that a run of launches needs no launch of its own to advance it:
+// count t stands in slot t & 1.  The first launch of a run reads its slot and
+// writes the advanced count to the other, which the rest read; the second
+// writes it back where the run's steps are even in number.  No launch writes
+// the slot it reads (its workgroups do not all run at one time), and launches
+// of a fixed parity, which a captured graph holds, always find their slot.
+// A kernel reads at its start and ticks at its end, with its first thread: a
+// store before the loads of the state would hold them up (512^3 fp16 3%).
+struct Clock {
+  const uint64_t* now;
+  uint64_t off;
+  uint64_t* next;  // written with *now + add, or NULL
+  uint64_t add;
+  __device__ __forceinline__ uint64_t read() const { return *now + off; }
+  __device__ __forceinline__ void tick(uint64_t t) const {
+    if (next && threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) *next = t - off + add;
+  }
+};
+
 // ---------------------------------------------------------------- Philox4x32-10
 // Salmon, Moraes, Dror & Shaw (SC'11): ten rounds of two 32x32->64 products
 // of counter words 0 and 2 with the published multipliers, feeding the high
@@ -510,13 +532,13 @@ __device__ __forceinline__ uint32_t find_lattice(const uint32_t* __restrict__ bl
 }
 
 // ---------------------------------------------------------------- step kernel
-// One fused collide-and-stream step at step count t = *d_t + t_off with
+// One fused collide-and-stream step at the clock's step count t with
 // parity P = t & 1, for every site of every lattice in lats[0..nlat), with
 // the streaming or (RES) the resident cache policy.
 template <class M, int S, int P, bool WIDE, int BLOCK, bool RES>
 __global__ void __launch_bounds__(BLOCK)
 k_step(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, uint32_t nlat,
-       uint32_t remap, const uint64_t* __restrict__ d_t, uint32_t t_off) {
+       uint32_t remap, Clock ck) {
   using Off = typename std::conditional<WIDE, uint64_t, uint32_t>::type;
   using C = Codec<S>;
   constexpr int Q = M::Q;
@@ -527,7 +549,7 @@ k_step(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, uint3
   const uint32_t b0 = (nlat > 1) ? blk[l] : 0u;
   const uint32_t site = (b - b0) * BLOCK + threadIdx.x;
   if (site >= L.nsites) return;
-  const uint64_t t = *d_t + t_off;
+  const uint64_t t = ck.read();
 
   float d[Q];
   Off o[Q];
@@ -562,6 +584,7 @@ k_step(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, uint3
       st<T, pol(CP::nt_store(plane))>(L, plane, o[i], C::enc(d[i]));
     });
   }
+  ck.tick(t);
 }
 
 // ---------------------------------------------------------------- step kernel, row tiling
@@ -575,7 +598,7 @@ k_step(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, uint3
 template <class M, int S, int P, int BLOCK, bool RES>
 __global__ void __launch_bounds__(BLOCK)
 k_step_rows(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, uint32_t nlat,
-            uint32_t remap, const uint64_t* __restrict__ d_t, uint32_t t_off) {
+            uint32_t remap, Clock ck) {
   using C = Codec<S>;
   using T = typename C::T;
   using CP = CachePolicy<M, S, P, RES>;
@@ -591,12 +614,12 @@ k_step_rows(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, 
   const uint32_t row = fastdiv(bl, L.ds_m, L.ds_s1, L.ds_s2);
   const uint32_t x = (bl - row * L.segs) * BLOCK + threadIdx.x;
   if (x >= L.nx) return;
+  const uint64_t t = ck.read();
   uint32_t z = 0, y = row;  // a 2D lattice has nz = 1
   if constexpr (M::D == 3) {
     z = fastdiv(row, L.dy_m, L.dy_s1, L.dy_s2);
     y = row - z * L.ny;
   }
-  const uint64_t t = *d_t + t_off;
   const uint32_t site = x + row * L.nx;
 
   // uniform row offsets (elements) of the y/z neighbours, periodic
@@ -669,6 +692,7 @@ k_step_rows(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, 
       else Raw<T>::template st<0>(plane_rsrc(L, j, ES), vx, C::enc(d[j]), ro * ES);
     }
   }
+  ck.tick(t);
 }
 
 // ---------------------------------------------------------------- propagation only
@@ -683,7 +707,7 @@ k_step_rows(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, 
 template <class M, int S, int P, bool WIDE, int BLOCK, bool RES>
 __global__ void __launch_bounds__(BLOCK)
 k_propagate(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, uint32_t nlat,
-            uint32_t remap, const uint64_t* __restrict__ d_t, uint32_t t_off) {
+            uint32_t remap, Clock ck) {
   using Off = typename std::conditional<WIDE, uint64_t, uint32_t>::type;
   using T = typename Codec<S>::T;
   using CP = CachePolicy<M, S, P, RES>;
@@ -715,12 +739,13 @@ k_propagate(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, 
     constexpr int plane = P == 0 ? M::OPP[i] : i;
     st<T, pol(CP::nt_store(plane))>(L, plane, o[i], h[i]);
   });
+  if (ck.next) ck.tick(ck.read());
 }
 
 template <class M, int S, int P, int BLOCK, bool RES>
 __global__ void __launch_bounds__(BLOCK)
 k_propagate_rows(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, uint32_t nlat,
-                 uint32_t remap, const uint64_t* __restrict__ d_t, uint32_t t_off) {
+                 uint32_t remap, Clock ck) {
   using T = typename Codec<S>::T;
   using CP = CachePolicy<M, S, P, RES>;
   constexpr int EP = pol(CP::nt_load(0));  // the even step's one policy for every plane
@@ -747,6 +772,7 @@ k_propagate_rows(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ 
     for (int i = 0; i < Q; ++i) h[i] = Raw<T>::template ld<EP>(plane_rsrc(L, i, ES), bx, r0 * ES);
 #pragma unroll
     for (int i = 0; i < Q; ++i) Raw<T>::template st<EP>(plane_rsrc(L, M::OPP[i], ES), bx, h[i], r0 * ES);
+    if (ck.next) ck.tick(ck.read());
     return;
   }
   const uint32_t ym = (y == 0) ? L.wy : 0u - L.nx;
@@ -772,6 +798,7 @@ k_propagate_rows(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ 
     if (CP::nt_store(j)) Raw<T>::template st<CPOL_NT>(plane_rsrc(L, j, ES), vx[j], h[j], ro[j] * ES);
     else Raw<T>::template st<0>(plane_rsrc(L, j, ES), vx[j], h[j], ro[j] * ES);
   }
+  if (ck.next) ck.tick(ck.read());
 }
 
 // ---------------------------------------------------------------- fused passes
@@ -788,10 +815,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t span_rsrc(uint64_t a, uint32_t
   return __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)a, 0, (int)span, RAW_BUFFER_WORD3);
 }
 
-// Advance the device step counter after a run of step kernels.
-__global__ void k_advance(uint64_t* d_t, uint64_t n) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *d_t += n;
-}
 __global__ void k_set_t(uint64_t* d_t, uint64_t t) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *d_t = t;
 }

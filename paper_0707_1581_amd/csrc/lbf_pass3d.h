@@ -78,8 +78,7 @@ struct PassGeom {
 
 template <int S, bool PROP, bool PULL, bool OWN, bool NT>
 __global__ void __launch_bounds__(P3_THREADS)
-k_pass3d(const LatDesc* __restrict__ src, PassSide from, PassSide to, const uint64_t* __restrict__ d_t,
-         uint32_t t_off, PassGeom g) {
+k_pass3d(const LatDesc* __restrict__ src, PassSide from, PassSide to, Clock ck, PassGeom g) {
   using M = D3Q19;
   using C = Codec<S>;
   using T = typename C::T;
@@ -100,7 +99,7 @@ k_pass3d(const LatDesc* __restrict__ src, PassSide from, PassSide to, const uint
   const uint32_t x0 = txi * g.tx, y0 = tyi * g.ty, z0 = tzi * g.len;
   const uint32_t TW = min(g.tx, nx - x0), TH = min(g.ty, ny - y0), ZC = min(g.len, nz - z0);
   const uint32_t NIT = ZC + 2u;  // phase it: first step of plane z0 + it - 1, second of the one before
-  const uint64_t t = *d_t + t_off;
+  const uint64_t t = ck.read();
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
 
   // this lane's site in tile coordinates plus one, 0..TW + 1 and 0..TH + 1;
@@ -242,6 +241,7 @@ k_pass3d(const LatDesc* __restrict__ src, PassSide from, PassSide to, const uint
   };
   if (w < (uint32_t)P3_TY) walk(std::true_type{});
   else walk(std::false_type{});
+  ck.tick(t);
 }
 
 }  // namespace lbf

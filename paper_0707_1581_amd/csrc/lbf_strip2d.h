@@ -70,8 +70,7 @@ __device__ __forceinline__ T lane_from(T v) {
 
 template <int S, bool PROP, int K>
 __global__ void __launch_bounds__(64 * S2_WAVES)
-k_strip2d(const LatDesc* __restrict__ src, PassSide from, PassSide to, const uint64_t* __restrict__ d_t,
-          uint32_t t_off, StripGeom g) {
+k_strip2d(const LatDesc* __restrict__ src, PassSide from, PassSide to, Clock ck, StripGeom g) {
   using M = D2Q9;
   using C = Codec<S>;
   using T = typename C::T;
@@ -86,11 +85,11 @@ k_strip2d(const LatDesc* __restrict__ src, PassSide from, PassSide to, const uin
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wid = xcd_remap(blockIdx.x, gridDim.x, 1) * S2_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (wid >= g.ntx * g.nty) return;
+  const uint64_t t = ck.read();
   const uint32_t txi = wid % g.ntx, tyi = wid / g.ntx;
   const uint32_t x0 = txi * g.tx, y0 = tyi * g.len;
   const uint32_t TW = min(g.tx, nx - x0), YC = min(g.len, ny - y0);
   const uint32_t NIT = YC + 2u * HALO;
-  const uint64_t t = *d_t + t_off;
 
   // this lane's column: lanes past the strip and its halo repeat the last one
   const uint32_t col = min(lane, TW + 2u * HALO - 1u);
@@ -187,6 +186,7 @@ k_strip2d(const LatDesc* __restrict__ src, PassSide from, PassSide to, const uin
     for (int k = K - 1; k > 0; --k) yr[k] = yr[k - 1];
     yr[0] = yn;
   }
+  ck.tick(t);
 }
 
 }  // namespace lbf
