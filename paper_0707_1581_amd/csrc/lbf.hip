@@ -308,7 +308,7 @@ struct lb_ctx {
   std::vector<uint64_t> offsets;
   int64_t t = 0;                // host mirror of d_t[t & 1]
 
-  // device metadata: [d_t (2 slots) | result (5 doubles) | pad] [partials] [lats] [lats in tile order] [blk]
+  // device metadata: [d_t (2 slots) | pad] [partials] [lats] [lats in tile order] [blk]
   char* d_meta = nullptr;
   uint64_t* d_t = nullptr;
   double* d_result = nullptr;
@@ -317,7 +317,7 @@ struct lb_ctx {
   LatDesc* d_tile_lats = nullptr;
   uint32_t* d_blk = nullptr;
   uint32_t* d_blk_rows = nullptr;   // tile prefix of the row tiling
-  double* h_result = nullptr;   // pinned
+  double* h_result = nullptr;   // pinned, d_result its device address
   std::vector<LatDesc> lats;
 
   lb_schedule sched{256, 0, 16, {0, 0}, {1, 0}, 0, 0, 0};
@@ -875,7 +875,6 @@ int alloc_meta(lb_ctx* c) {
   const size_t total = small_off + small;
   HIP_TRY(hipMalloc(&c->d_meta, total));
   c->d_t = reinterpret_cast<uint64_t*>(c->d_meta);
-  c->d_result = reinterpret_cast<double*>(c->d_meta + 64);
   c->d_partial = reinterpret_cast<double*>(c->d_meta + head);
   c->d_lats = reinterpret_cast<LatDesc*>(c->d_meta + head + up(part));
   c->d_tile_lats = reinterpret_cast<LatDesc*>(c->d_meta + head + up(part) + up(lats));
@@ -883,6 +882,7 @@ int alloc_meta(lb_ctx* c) {
   c->d_blk_rows = reinterpret_cast<uint32_t*>(c->d_meta + head + up(part) + 2 * up(lats) + up(blk));
   if (small) c->d_small_b = c->d_meta + small_off;
   HIP_TRY(hipHostMalloc((void**)&c->h_result, sizeof(double) * 5, hipHostMallocDefault));
+  HIP_TRY(hipHostGetDevicePointer((void**)&c->d_result, c->h_result, 0));
   HIP_TRY(hipMemcpy(c->d_lats, c->lats.data(), lats, hipMemcpyHostToDevice));
   return LB_OK;
 }
@@ -1202,10 +1202,11 @@ int lb_check(lb_ctx* ctx, int64_t* n_bad, double* sums_out) {
   const LatDesc* L = r->d_lats + v.idx;
   double* part = r->d_partial;
   void* args[] = {&L, &part};
-  HIP_TRY(hipLaunchKernel(fn, dim3(CHECK_BLOCKS), dim3(256), args, 0, r->stream));
-  hipLaunchKernelGGL(k_check_final, dim3(1), dim3(64), 0, r->stream, r->d_partial, CHECK_BLOCKS, r->d_result);
+  const uint64_t n = sites_of(r->reps[v.idx]);
+  const int blocks = (int)std::min<uint64_t>(CHECK_BLOCKS, (n + 255) / 256);
+  HIP_TRY(hipLaunchKernel(fn, dim3(blocks), dim3(256), args, 0, r->stream));
+  hipLaunchKernelGGL(k_check_final, dim3(1), dim3(CHECK_FINAL), 0, r->stream, r->d_partial, blocks, r->d_result);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipMemcpyAsync(r->h_result, r->d_result, sizeof(double) * 5, hipMemcpyDeviceToHost, r->stream));
   HIP_TRY(hipStreamSynchronize(r->stream));
   const lb_params& p = r->reps[v.idx];
   const int64_t bad = (int64_t)r->h_result[0];
