@@ -210,11 +210,18 @@ class _Gathers:
         caller's current stream may use at once."""
         lat_stream = self.stream if isinstance(self, Lattice) else self._ens.stream
         out = torch.empty((rows, *self._dims()), dtype=torch.float32, device=self.device)
-        _adopt(out, self.device, lat_stream)
-        _check(fn(self._ctx, _aligned(out)), name)
-        cur = torch.cuda.current_stream(self.device)
-        if lat_stream != cur:
-            cur.wait_stream(lat_stream)
+        # the handles alone are compared (a torch.cuda.Stream for the current
+        # stream takes as long as a gather of a small lattice); the streams
+        # are ordered as by _adopt where they differ
+        index = self.device.index if self.device.index is not None else torch.cuda.current_device()
+        other = torch._C._cuda_getCurrentRawStream(index) != lat_stream.cuda_stream
+        if other:
+            _adopt(out, self.device, lat_stream)
+        rc = fn(self._ctx, _aligned(out))
+        if rc != LB_OK:
+            _check(rc, name)
+        if other:
+            torch.cuda.current_stream(self.device).wait_stream(lat_stream)
         return out
 
     def populations(self):
