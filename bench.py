@@ -37,7 +37,8 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 W36 = [36, 12, 12, 12, 24, 48, 16, 4, 4, 4, 24, 24, 24, 8, 8, 8, 72, 48, 16]  # 36 w_k, Table II
 W36_D2Q9 = [36, 12, 12, 144, 16, 4, 24, 24, 576]  # 36 w_k, Table I
-KERNEL_SOURCES = ["paper_0707_1581_amd/csrc/lbf_kernels.h", "paper_0707_1581_amd/csrc/lbf_math.h"]
+KERNEL_SOURCES = [f"paper_0707_1581_amd/csrc/{f}" for f in
+                  ("lbf_kernels.h", "lbf_math.h", "lbf_pass3d.h", "lbf_strip2d.h", "lbf_block.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_step_512.json")
 VALU_FILE = os.path.join(ROOT, "profiles", "valu_step.json")
 # VALU issue budget: 256 CUs x 4 SIMDs at 2.4 GHz; a wave64 fp32 add/mul/fma issues in 2 cycles,

@@ -370,11 +370,13 @@ struct lb_ctx {
   PassPlan plans[PASS_MAX + 1];  // by the steps of a pass, from 2
   int pass_max = 2;
   bool blocks = false;           // small lattice: every pass is k_block
-  // Small lattices run passes of several steps before any schedule is set,
-  // through a second buffer of their own in d_meta.
+  // Small lattices, and 16-bit D2Q9 ones a little beyond the cache, run passes
+  // of several steps before any schedule is set, through a second buffer in
+  // d_meta (small ones) or d_state_b.
   char* d_small_b = nullptr;
-  bool small_passes = false;
-  bool passes(bool prop) const { return sched.fused || (small_passes && !prop); }
+  bool default_passes = false;
+  bool passes(bool prop) const { return sched.fused || (default_passes && !prop); }
+  bool uses_state_b() const { return sched.fused || (default_passes && !d_small_b); }
   struct PassArgs {
     const LatDesc* src;
     PassSide from, to;
@@ -450,14 +452,15 @@ bool block_passes(const lb_params& p) {
 
 // Bytes of the second buffer of a small lattice, which takes several steps per
 // launch (k_block) by default: D3Q19 of up to 16384 sites (16^3 fp32 3.2 us per
-// step, AA 3.9), D2Q9 of up to 16 MB in fp32 (64 x 48 1.75 against 3.5 us,
-// 512^2 4.4 against 5.5) and 5 MB in 16 bits (512^2 bf16 4.7 against 4.8; 1024^2
-// 11.4 against 11.3).  0 for a larger lattice or a batch.
+// step, AA 3.9), D2Q9 of up to 32 MiB in fp32 (64 x 48 1.75 against 3.5 us,
+// 512^2 4.4 against 5.5, 724^2 6.5 against 8.4; beyond, the schedule is fused)
+// and 5 MB in 16 bits (512^2 bf16 4.7 against 4.8; 1024^2 11.4 against 11.3).  0
+// for a larger lattice or a batch.
 size_t small_bytes(const lb_ctx* c) {
   if (c->reps.size() != 1) return 0;
   const lb_params& p = c->reps[0];
   const size_t bytes = (size_t)q_of(p.lattice) * sites_of(p) * elem_size(p.storage);
-  if (p.lattice == LB_D2Q9) return bytes <= (p.storage == LB_F32 ? 16000000u : 5000000u) ? bytes : 0;
+  if (p.lattice == LB_D2Q9) return bytes <= (p.storage == LB_F32 ? 32u << 20 : 5000000u) ? bytes : 0;
   return block_passes(p) ? bytes : 0;
 }
 
@@ -727,7 +730,7 @@ lb_ctx::PassArgs pass_args(const lb_ctx* c, const Clock& clock, const std::vecto
   const uint32_t slice = c->lattice == LB_D2Q9 ? row : row * L.ny;
   const PassSide A{L.base, L.plane * elem_size(c->storage), slice, row, slice};
   PassSide B = A;
-  B.base = (uint64_t)(uintptr_t)(c->sched.fused ? c->d_state_b : c->d_small_b);
+  B.base = (uint64_t)(uintptr_t)(c->uses_state_b() ? c->d_state_b : c->d_small_b);
   if (second_rows(c->reps[0])) {
     const uint32_t pitch = (uint32_t)second_pitch(c->reps[0]), q = (uint32_t)q_of(c->lattice);
     B.plane = pitch;
@@ -842,7 +845,7 @@ int advance(lb_ctx* c, int64_t n) {
   // the host stays ahead of them, and all n steps are divided among the passes
   // at once (20 steps of 16384^2 fp32: 34.9 ms, as a replay of 16 and 4 more
   // 38.0).
-  const bool long_passes = c->sched.fused && c->lats[0].plane * q_of(c->lattice) * elem_size(c->storage) >= 64000000;
+  const bool long_passes = c->passes(false) && c->lats[0].plane * q_of(c->lattice) * elem_size(c->storage) >= 64000000;
   const bool graphable = (uint64_t)K * c->groups.size() <= (1u << 16) && !long_passes;
   if (n >= K && graphable) {
     if (!c->graph_exec) {
@@ -871,9 +874,14 @@ int alloc_meta(lb_ctx* c) {
   const size_t lats = sizeof(LatDesc) * nlat;
   const size_t blk = sizeof(uint32_t) * (nlat + 1);
   auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
-  const size_t small = small_bytes(c), small_off = head + up(part) + 2 * up(lats) + 2 * up(blk);
-  const size_t total = small_off + small;
-  HIP_TRY(hipMalloc(&c->d_meta, total));
+  const size_t small_off = head + up(part) + 2 * up(lats) + 2 * up(blk);
+  size_t small = small_bytes(c);
+  if (small && hipMalloc(&c->d_meta, small_off + small) != hipSuccess) {  // no room: one step per launch
+    (void)hipGetLastError();
+    c->d_meta = nullptr;
+    small = 0;
+  }
+  if (!c->d_meta) HIP_TRY(hipMalloc(&c->d_meta, small_off));
   c->d_t = reinterpret_cast<uint64_t*>(c->d_meta);
   c->d_partial = reinterpret_cast<double*>(c->d_meta + head);
   c->d_lats = reinterpret_cast<LatDesc*>(c->d_meta + head + up(part));
@@ -988,20 +996,26 @@ int default_schedule(lb_ctx* c) {
   // against 1.84 ms per step; 4096^2, inside it, 111 against 118 us; 2048^2 36
   // against 31).  So does 16-bit D3Q19 state without noise on boxes that fill the
   // tiles (512^3 fp16 1.45 against 1.96 ms; 256^3 192 against 208 us; 400 x 300 x
-  // 350, 86% filled, 636 against 655, 200 x 234 x 342, 76%, 8% slower); with noise the collisions bound
-  // the pass (512^3 fp16 1.99 against 1.85 ms) and it keeps one step per launch.
+  // 350, 86% filled, 636 against 655; 200 x 234 x 342, 76%, 8% slower); with
+  // noise the collisions bound the pass (512^3 fp16 1.99 against 1.85 ms) and it
+  // keeps one step per launch.
   const bool d2 = c->lattice == LB_D2Q9, f32 = c->storage == LB_F32;
   const uint64_t fused_above = f32 ? (d2 ? 32 * MIB : 256 * MIB) : 320 * MB;
   const bool pays = d2 || f32 || (c->reps[0].kT == 0.0 && tile_fill(c->reps[0]) >= 0.9);
-  c->small_passes = c->d_small_b != nullptr;
-  if (pays && fused_eligible(c) && total > fused_above) {
+  c->default_passes = c->d_small_b != nullptr;
+  // 16-bit D2Q9 between the cache and that bound: passes too, unless a schedule
+  // is set (4096 x 4099 fp16 108 against 119 us, bf16 111 against 119; 3001 x
+  // 2777, 150 MB, 58.4 and 58.6).
+  const bool beyond_cache = d2 && !f32 && total > 256 * MIB;
+  if (fused_eligible(c) && ((pays && total > fused_above) || beyond_cache)) {
     const std::string keep = g_last_error;
     size_t free_b = 0, total_b = 0;
     // 16-bit state: only where the second buffer is a small part of what is
     // free, so that large 16-bit lattices keep the memory they are chosen for
     const bool room = f32 || (hipMemGetInfo(&free_b, &total_b) == hipSuccess && 4 * total <= free_b);
-    if (room && ensure_state_b(c) == LB_OK) c->sched.fused = 1;
-    else g_last_error = keep;  // no room: one step per launch, not an error
+    if (!room || ensure_state_b(c) != LB_OK) g_last_error = keep;  // no room: one step per launch, not an error
+    else if (total > fused_above) c->sched.fused = 1;
+    else c->default_passes = true;
   }
   return upload_schedule(c);
 }
@@ -1414,7 +1428,7 @@ int lb_set_schedule(lb_ctx* ctx, const lb_schedule* s) {
     if (rc) return rc;
   }
   ctx->sched = *s;
-  ctx->small_passes = false;
+  ctx->default_passes = false;
   int rc = upload_schedule(ctx);
   if (!s->fused) release_state_b(ctx);
   return rc;
@@ -1540,8 +1554,8 @@ int autotune_timed(lb_ctx* ctx, int32_t steps, char* report, size_t report_len) 
     return fail(LB_EDEVICE, std::string("hipMemcpyAsync (autotune scratch copy): ") + hipGetErrorString(ce));
   }
 
-  const bool saved_small = ctx->small_passes;
-  ctx->small_passes = false;  // a tuned schedule is taken as it stands
+  const bool saved_small = ctx->default_passes;
+  ctx->default_passes = false;  // a tuned schedule is taken as it stands
   const std::vector<LatDesc> saved_lats = ctx->lats;
   const lb_schedule saved = ctx->sched;
   const int64_t saved_t = ctx->t;
@@ -1736,9 +1750,9 @@ int autotune_timed(lb_ctx* ctx, int32_t steps, char* report, size_t report_len) 
   (void)hipMemcpy(ctx->d_lats, ctx->lats.data(), sizeof(LatDesc) * ctx->lats.size(), hipMemcpyHostToDevice);
   hipLaunchKernelGGL(k_set_t, dim3(1), dim3(64), 0, ctx->stream, ctx->d_t + (saved_t & 1), (uint64_t)saved_t);
   ctx->sched = (rc == LB_OK) ? best : saved;
-  ctx->small_passes = rc != LB_OK && saved_small;
+  ctx->default_passes = rc != LB_OK && saved_small;
   int rc2 = upload_schedule(ctx);
-  if (!ctx->sched.fused) release_state_b(ctx);
+  if (!ctx->uses_state_b()) release_state_b(ctx);
   if (report && report_len) {
     std::strncpy(report, rep.c_str(), report_len - 1);
     report[report_len - 1] = 0;

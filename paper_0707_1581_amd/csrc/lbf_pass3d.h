@@ -22,14 +22,15 @@
 // Layouts.  Between the passes of one call the state need not be streamed: all
 // but the last pass store the second step's populations at their own site
 // (whole aligned rows, past the caches), and all but the first pull them from
-// r - c_i.  NT: the destination's rows are whole 128-byte lines; where they are
-// not, a tile's row ends inside lines, and streaming the parts costs more than
-// caching them (with the pitch of the second buffer, 441 x 318 x 225 fp32 takes
-// 651 us per step instead of 784).  The first pass reads and the last writes the even AA layout.  The
-// second buffer holds the 19 populations of an x-row side by side: with planes
-// on both sides a workgroup would have 38 pages or more in use at a time, more
-// than the CU's address translation cache holds (22e6 misses a pass at 512^3,
-// now 66e3; that alone took a pass from 6.59 to 5.53 ms).
+// r - c_i.  The first pass reads and the last writes the even AA layout.  NT:
+// the destination's rows are whole 128-byte lines; where they are not, a tile's
+// row ends inside lines, and streaming the parts costs more than caching them
+// (with the pitch of the second buffer, 441 x 318 x 225 fp32 takes 651 us per
+// step instead of 784).  The second buffer holds the 19 populations of an x-row
+// side by side: with planes on both sides a workgroup would have 38 pages or
+// more in use at a time, more than the CU's address translation cache holds
+// (22e6 misses a pass at 512^3, now 66e3; that alone took a pass from 6.59 to
+// 5.53 ms).
 //
 // What bounds it: the movement (4.1 ms of the pass with the identity
 // collision, 22.8 GB past the L2) and, nearly level with it, the collisions

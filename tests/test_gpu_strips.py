@@ -80,3 +80,29 @@ def test_strips_match_oracle(dims, steps):
         assert err < 1e-5, (dims, kT, err)  # the parity bar of the fp32 state
         start.close()
         lat.close()
+
+
+@pytest.mark.parametrize("storage,dims", [("f16", (4096, 3700)), ("bf16", (3900, 4001)), ("f32", (857, 911)),
+                                          ("f32", (1023, 901))])
+def test_passes_before_a_schedule_is_set(storage, dims):
+    """Lattices that report fused = 0 but take several steps per launch until
+    a schedule is set: the bits of single steps, also after a propagation and
+    once a schedule has been set."""
+    lats = [lbf.Lattice(dims[0], dims[1], 1, lattice="d2q9", storage=storage, kT=1e-4, gamma_bulk=0.5,
+                        gamma_shear=0.8, seed=11, init="thermal", t0=3) for _ in range(2)]
+    assert lats[0].schedule()["fused"] == 0
+    lats[1].set_schedule(fused=0)
+    for n in (4, 1, 19, 32, 7):
+        for lat in lats:
+            lat.step(n)
+        assert torch.equal(lats[0].state, lats[1].state), n
+    for lat in lats:
+        lat.propagate(3)
+        lat.step(6)
+    assert torch.equal(lats[0].state, lats[1].state)
+    lats[0].set_schedule(fused=0)
+    for lat in lats:
+        lat.step(17)
+    assert torch.equal(lats[0].state, lats[1].state)
+    for lat in lats:
+        lat.close()
