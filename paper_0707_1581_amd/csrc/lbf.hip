@@ -203,8 +203,8 @@ void* rows_ptr(int lattice, int storage, int parity, bool res, int block, bool p
                             : rows_ptr_m<D3Q19, false>(storage, parity, res, block);
 }
 
-// Fused passes of k steps per launch (D3Q19: k = 2; D2Q9: k = 2, 3 or 4) and
-// their propagation-only twins.  pull, own: the D3Q19 pass reads, writes
+// Fused passes of k steps per launch (D3Q19: k = 2; D2Q9: k = 2, 3 or 4), of
+// workgroups of that many threads, and their propagation-only twins.  pull, own: the D3Q19 pass reads, writes
 // populations that are not streamed yet (between the passes of one call); nt:
 // the rows it writes are whole lines.
 template <int S, bool PROP, bool NT>
@@ -213,23 +213,28 @@ void* pass3d_ptr(bool pull, bool own) {
   return (void*)&k_pass3d<S, PROP, false, true, NT>;  // the first of two passes or more
 }
 template <int S, bool PROP>
-void* pass_ptr_s(int lattice, int k, bool pull, bool own, bool nt) {
-  if (lattice == LB_D2Q9)
-    return k == 4 ? (void*)&k_strip2d<S, PROP, 4> : k == 3 ? (void*)&k_strip2d<S, PROP, 3> : (void*)&k_strip2d<S, PROP, 2>;
+void* strip_ptr(int k, int threads) {
+  if constexpr (S == ST_F32)
+    if (threads == 64 * S2_WIDE_WAVES) return (void*)&k_strip2d<S, PROP, 2, S2_WIDE_WAVES>;
+  return k == 4 ? (void*)&k_strip2d<S, PROP, 4> : k == 3 ? (void*)&k_strip2d<S, PROP, 3> : (void*)&k_strip2d<S, PROP, 2>;
+}
+template <int S, bool PROP>
+void* pass_ptr_s(int lattice, int k, int threads, bool pull, bool own, bool nt) {
+  if (lattice == LB_D2Q9) return strip_ptr<S, PROP>(k, threads);
   return nt ? pass3d_ptr<S, PROP, true>(pull, own) : pass3d_ptr<S, PROP, false>(pull, own);
 }
 template <bool PROP>
-void* pass_ptr_p(int lattice, int storage, int k, bool pull, bool own, bool nt) {
+void* pass_ptr_p(int lattice, int storage, int k, int threads, bool pull, bool own, bool nt) {
   switch (storage) {
-    case LB_F32: return pass_ptr_s<ST_F32, PROP>(lattice, k, pull, own, nt);
-    case LB_F16: return pass_ptr_s<ST_F16, PROP>(lattice, k, pull, own, nt);
-    case LB_BF16: return pass_ptr_s<ST_BF16, PROP>(lattice, k, pull, own, nt);
+    case LB_F32: return pass_ptr_s<ST_F32, PROP>(lattice, k, threads, pull, own, nt);
+    case LB_F16: return pass_ptr_s<ST_F16, PROP>(lattice, k, threads, pull, own, nt);
+    case LB_BF16: return pass_ptr_s<ST_BF16, PROP>(lattice, k, threads, pull, own, nt);
   }
   return nullptr;
 }
-void* pass_ptr(int lattice, int storage, int k, bool pull, bool own, bool nt, bool prop) {
-  return prop ? pass_ptr_p<true>(lattice, storage, k, pull, own, nt)
-              : pass_ptr_p<false>(lattice, storage, k, pull, own, nt);
+void* pass_ptr(int lattice, int storage, int k, int threads, bool pull, bool own, bool nt, bool prop) {
+  return prop ? pass_ptr_p<true>(lattice, storage, k, threads, pull, own, nt)
+              : pass_ptr_p<false>(lattice, storage, k, threads, pull, own, nt);
 }
 
 // Fused passes of small lattices, by the lanes of a workgroup.
@@ -526,20 +531,26 @@ int plan_passes(lb_ctx* c) {
     return LB_OK;
   }
   c->pass_max = 2;
+  // D2Q9 state beyond the Infinity Cache: strips in step (see k_strip2d; 16384^2
+  // fp32 1.84 to 1.62 ms per step over 20 steps, bf16 1.61 to 1.55; 4096^2 bf16,
+  // 302 MB, 109 to 111 us, 1400 x 1500 fp32, 76 MB, 18.9 to 19.3)
+  const bool sync = L.plane * q_of(c->lattice) * elem_size(c->storage) > 320000000;
   for (int k = 2; k <= (c->lattice == LB_D2Q9 ? 4 : 2); ++k) {
     lb_ctx::PassPlan& p = c->plans[k];
-    p.threads = c->lattice == LB_D2Q9 ? 64 * S2_WAVES : P3_THREADS;
+    const uint32_t waves = sync && k == 2 && c->storage == LB_F32 ? S2_WIDE_WAVES : S2_WAVES;
+    p.threads = c->lattice == LB_D2Q9 ? 64 * (int)waves : P3_THREADS;
     int per_cu = 0;
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pass_ptr(c->lattice, c->storage, k, true, true, true, false), p.threads, 0));
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pass_ptr(c->lattice, c->storage, k, p.threads, true, true, true, false), p.threads, 0));
     const uint32_t slots = (uint32_t)std::max(1, cus * per_cu);  // workgroups resident at a time
     if (c->lattice == LB_D2Q9) {
       StripGeom& g = p.strip;
       const uint32_t w = 64u - 2u * (uint32_t)(k - 1);
       g.ntx = (L.nx + w - 1u) / w;
       g.tx = (L.nx + g.ntx - 1u) / g.ntx;
-      g.len = strip_rows(g.ntx, L.ny, slots * S2_WAVES);
+      g.len = strip_rows(g.ntx, L.ny, slots * waves);
       g.nty = (L.ny + g.len - 1u) / g.len;
-      p.grid = dim3((g.ntx * g.nty + S2_WAVES - 1u) / S2_WAVES);
+      g.sync = sync;
+      p.grid = dim3((g.ntx * g.nty + waves - 1u) / waves);
       // Strips of few rows spend more on the wider halo of four steps than
       // they save (1024^2 fp32, 4 rows: 14.2 us per step, with two 12.9;
       // 2048^2, 15 rows: 34.0 and 37.9).
@@ -703,8 +714,8 @@ int launch_step(lb_ctx* c, lb_ctx::Run& run, uint64_t s, int parity, bool prop =
 // steps (the layout they leave is that of an even t); the rest, fewer than
 // four steps, runs as AA steps.  Where passes of four steps pay, as few passes
 // as cover the steps, of sizes as equal as they can be: a pass of two moves as
-// many bytes as one of four (16384^2 fp32: passes of 2, 3 and 4 steps take 5.5,
-// 4.9 and 6.3 ms), so 20 steps are 4 + 4 + 3 + 3 + 3 + 3.
+// many bytes as one of four (16384^2 fp32: passes of 2, 3 and 4 steps take 4.0,
+// 4.9 and 6.4 ms), so 20 steps are 4 + 4 + 3 + 3 + 3 + 3.
 std::vector<int> pass_steps(const lb_ctx* c, int64_t m) {
   const int64_t most = c->pass_max;
   int64_t left = m & ~(int64_t)1, passes = 2 * (left / (2 * most));
@@ -743,7 +754,7 @@ lb_ctx::PassArgs pass_args(const lb_ctx* c, const Clock& clock, const std::vecto
   bg.to = to_b ? B.base : A.base;
   return {c->d_lats, to_b ? A : B, to_b ? B : A, clock, p.tiles, p.strip, bg,
           c->blocks ? block_ptr(c->lattice, c->storage, p.threads, prop)
-                    : pass_ptr(c->lattice, c->storage, ks[n], n > 0, n + 1 < ks.size(),
+                    : pass_ptr(c->lattice, c->storage, ks[n], p.threads, n > 0, n + 1 < ks.size(),
                                (to_b ? (uint32_t)B.plane : row) % 128 == 0, prop)};
 }
 

@@ -1,4 +1,4 @@
-// Fused steps of a D2Q9 lattice: K per launch (2 or 4).
+// Fused steps of a D2Q9 lattice: K per launch (2 to 4).
 //
 // k_strip2d advances a D2Q9 lattice from even t by K steps in one pass over
 // memory: it reads the state in the even AA layout (plane i at site r holds
@@ -20,11 +20,20 @@
 // to move use an offset beyond the descriptor, which the range check drops, so
 // the compiler can wait for exactly the loads it needs.
 //
-// What bounds it: the issue of vector instructions (with 16-bit storage the
-// pass takes as long as the collisions alone).  16384^2, per step: fp32 1.57
-// ms (1.23 of 8 TB/s in algorithmic bytes) against 2.17 for the former two-step
-// pass (256-site segments with an LDS ring) and 3.36 for AA steps; bf16 1.49
-// against 1.86 and 1.76.  K = 2 alone takes 2.76 and 1.52 ms.
+// The strips of a workgroup share lines at their edges, but no data.  With
+// sync they walk in step all the same, one barrier a phase, so that such a line
+// is read once and leaves the L2 whole: state that streams through HBM gains
+// (16384^2 fp32, 2.87 to 2.39 ms per step with K = 2 and 2.02 with 16 strips
+// side by side, 2.00 to 1.62 with K = 3, 1.61 as before with K = 4, which its
+// collisions hold in step; the second buffer's writes in partial lines were
+// 12% at K = 2), state the Infinity Cache holds loses 1-2%.  All waves run the
+// same phases, those past the last strip or row without effect.
+//
+// What bounds it: the issue of vector instructions for K = 3 and 4 (bf16 takes
+// as long as the collisions alone).  16384^2, 20 steps, per step: fp32 1.62 ms
+// (1.19 of 8 TB/s in algorithmic bytes) against 2.17 for the former two-step
+// pass (256-site segments with an LDS ring) and 3.36 for AA steps; bf16 1.55
+// against 1.86 and 1.76.
 //
 // Addressing.  One descriptor per row of one population, so a plane may exceed
 // 4 GiB.  The second buffer holds the nine populations of a row side by side:
@@ -45,9 +54,12 @@ struct StripGeom {
   uint32_t tx;   // interior sites of a strip, at most 64 - 2 (K - 1)
   uint32_t nty;  // chunks of rows
   uint32_t len;  // rows of a chunk
+  uint32_t sync;  // the strips of a workgroup walk in step
 };
 
-constexpr int S2_WAVES = 4;  // strips of a workgroup: independent waves
+// Strips of a workgroup, side by side: four, or 16 where the movement bounds
+// the pass (two fp32 steps, in step with each other).
+constexpr int S2_WAVES = 4, S2_WIDE_WAVES = 16;
 
 template <class M> struct YIndex {
   static constexpr int idx(int i) {
@@ -68,8 +80,8 @@ __device__ __forceinline__ T lane_from(T v) {
   else return __builtin_bit_cast(T, (uint16_t)u);
 }
 
-template <int S, bool PROP, int K>
-__global__ void __launch_bounds__(64 * S2_WAVES)
+template <int S, bool PROP, int K, int W = S2_WAVES>
+__global__ void __launch_bounds__(64 * W)
 k_strip2d(const LatDesc* __restrict__ src, PassSide from, PassSide to, Clock ck, StripGeom g) {
   using M = D2Q9;
   using C = Codec<S>;
@@ -83,13 +95,13 @@ k_strip2d(const LatDesc* __restrict__ src, PassSide from, PassSide to, Clock ck,
   Coef<M> cf(L);
   const uint32_t nx = L.nx, ny = L.ny;
   const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t wid = xcd_remap(blockIdx.x, gridDim.x, 1) * S2_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (wid >= g.ntx * g.nty) return;
+  const uint32_t wave = xcd_remap(blockIdx.x, gridDim.x, 1) * W + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t wid = min(wave, g.ntx * g.nty - 1u);  // waves past the last strip walk it too and store nothing
   const uint64_t t = ck.read();
   const uint32_t txi = wid % g.ntx, tyi = wid / g.ntx;
   const uint32_t x0 = txi * g.tx, y0 = tyi * g.len;
   const uint32_t TW = min(g.tx, nx - x0), YC = min(g.len, ny - y0);
-  const uint32_t NIT = YC + 2u * HALO;
+  const uint32_t NIT = wave == wid ? YC + 2u * HALO : 0u;
 
   // this lane's column: lanes past the strip and its halo repeat the last one
   const uint32_t col = min(lane, TW + 2u * HALO - 1u);
@@ -147,7 +159,8 @@ k_strip2d(const LatDesc* __restrict__ src, PassSide from, PassSide to, Clock ck,
     for (int i = 0; i < Q; ++i) h[i] = (H)0;
     store_row(yr[0], false, h);
   }
-  for (uint32_t it = 0; it < NIT; ++it) {
+  for (uint32_t it = 0; it < g.len + 2u * HALO; ++it) {
+    if (g.sync) __builtin_amdgcn_s_barrier();
     H h[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
@@ -181,7 +194,7 @@ k_strip2d(const LatDesc* __restrict__ src, PassSide from, PassSide to, Clock ck,
         }
       }
     });
-    store_row(yr[K - 1], it >= 2u * HALO, h);
+    store_row(yr[K - 1], it >= 2u * HALO && it < NIT, h);
 #pragma unroll
     for (int k = K - 1; k > 0; --k) yr[k] = yr[k - 1];
     yr[0] = yn;
