@@ -214,8 +214,10 @@ void* pass3d_ptr(bool pull, bool own) {
 }
 template <int S, bool PROP>
 void* strip_ptr(int k, int threads) {
-  if constexpr (S == ST_F32)
+  if constexpr (S == ST_F32) {
     if (threads == 64 * S2_WIDE_WAVES) return (void*)&k_strip2d<S, PROP, 2, S2_WIDE_WAVES>;
+    if (threads == 32 * S2_WIDE_WAVES) return (void*)&k_strip2d<S, PROP, 2, S2_WIDE_WAVES / 2>;
+  }
   return k == 4 ? (void*)&k_strip2d<S, PROP, 4> : k == 3 ? (void*)&k_strip2d<S, PROP, 3> : (void*)&k_strip2d<S, PROP, 2>;
 }
 template <int S, bool PROP>
@@ -534,10 +536,16 @@ int plan_passes(lb_ctx* c) {
   // D2Q9 state beyond the Infinity Cache: strips in step (see k_strip2d; 16384^2
   // fp32 1.84 to 1.62 ms per step over 20 steps, bf16 1.61 to 1.55; 4096^2 bf16,
   // 302 MB, 109 to 111 us, 1400 x 1500 fp32, 76 MB, 18.9 to 19.3)
-  const bool sync = L.plane * q_of(c->lattice) * elem_size(c->storage) > 320000000;
+  const uint64_t bytes = L.plane * q_of(c->lattice) * elem_size(c->storage);
   for (int k = 2; k <= (c->lattice == LB_D2Q9 ? 4 : 2); ++k) {
     lb_ctx::PassPlan& p = c->plans[k];
-    const uint32_t waves = sync && k == 2 && c->storage == LB_F32 ? S2_WIDE_WAVES : S2_WAVES;
+    // Two fp32 steps, from 140 MB: 16 strips side by side (3000 x 2900, 313 MB,
+    // 85.5 to 73.6 us per step), below 200 MB, where they fill the chip too
+    // unevenly, eight (2048^2, 151 MB, 39.0 to 35.3, with 16 37.9 to 39.4; 1700^2,
+    // 104 MB, 22.8, with eight 23.2).
+    const bool wide = k == 2 && c->storage == LB_F32 && bytes > 140000000;
+    const bool sync = wide || bytes > 320000000;
+    const uint32_t waves = !wide ? S2_WAVES : bytes > 200000000 ? S2_WIDE_WAVES : S2_WIDE_WAVES / 2;
     p.threads = c->lattice == LB_D2Q9 ? 64 * (int)waves : P3_THREADS;
     int per_cu = 0;
     HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pass_ptr(c->lattice, c->storage, k, p.threads, true, true, true, false), p.threads, 0));

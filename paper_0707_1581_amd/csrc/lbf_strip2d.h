@@ -57,8 +57,8 @@ struct StripGeom {
   uint32_t sync;  // the strips of a workgroup walk in step
 };
 
-// Strips of a workgroup, side by side: four, or 16 where the movement bounds
-// the pass (two fp32 steps, in step with each other).
+// Strips of a workgroup, side by side: four, or 16 or eight where the movement
+// bounds the pass (two fp32 steps, in step with each other).
 constexpr int S2_WAVES = 4, S2_WIDE_WAVES = 16;
 
 template <class M> struct YIndex {

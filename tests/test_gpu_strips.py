@@ -109,11 +109,12 @@ def test_passes_before_a_schedule_is_set(storage, dims):
 
 
 @pytest.mark.parametrize("storage,dims", [("f32", (3001, 3011)), ("f32", (59, 153001)), ("f32", (200003, 47)),
+                                          ("f32", (61, 70001)), ("f32", (2111, 1999)),
                                           ("f16", (4801, 3903)), ("bf16", (117, 160001))])
 def test_strips_in_step(storage, dims):
-    """State beyond the Infinity Cache, whose strips walk in step: ragged last
-    strips, chunks and workgroups, workgroups over several chunks, passes of
-    two, three and four steps."""
+    """State whose strips walk in step (beyond the Infinity Cache, and passes of
+    two fp32 steps from 140 MB on): ragged last strips, chunks and workgroups,
+    workgroups over several chunks, passes of two, three and four steps."""
     lats = [lbf.Lattice(**_cfg(dims), storage=storage, init="thermal") for _ in range(2)]
     lats[0].set_schedule(fused=1)
     lats[1].set_schedule(fused=0)
