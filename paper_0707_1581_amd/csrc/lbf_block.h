@@ -130,7 +130,7 @@ k_block(const LatDesc* __restrict__ src, Clock ck, BlockGeom g) {
                        (M::CZ[i] > 0 ? zp : (M::CZ[i] < 0 ? zm : z0));
     Raw<T>::template st<0>(out, mine ? s * ES : NOWHERE, own[i], (uint32_t)i * pbytes);
   }
-  ck.tick(t);
+  ck.tick(t, ck.ticks());
 }
 
 }  // namespace lbf

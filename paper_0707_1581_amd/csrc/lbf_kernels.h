@@ -86,15 +86,23 @@ __device__ __forceinline__ uint32_t fastdiv(uint32_t n, uint32_t m, uint32_t s1,
 // the slot it reads (its workgroups do not all run at one time), and launches
 // of a fixed parity, which a captured graph holds, always find their slot.
 // A kernel reads at its start and ticks at its end, with its first thread: a
-// store before the loads of the state would hold them up (512^3 fp16 3%).
+// store before the loads of the state would hold them up (512^3 fp16 3%).  Which
+// wave ticks is found at the start, as a scalar, and its first lane from the
+// lane id at the end: the thread index, live through a collision, is the
+// register that costs the flat odd D3Q19 step its seventh wave (73 of 72).  The
+// kernels that LDS bounds ask at the end, where a scalar would be spilled.
 struct Clock {
   const uint64_t* now;
   uint64_t off;
   uint64_t* next;  // written with *now + add, or NULL
   uint64_t add;
   __device__ __forceinline__ uint64_t read() const { return *now + off; }
-  __device__ __forceinline__ void tick(uint64_t t) const {
-    if (next && threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) *next = t - off + add;
+  // whether this wave ticks; asked where lane 0 of the grid's first wave is active
+  __device__ __forceinline__ bool ticks() const {
+    return next && (__builtin_amdgcn_readfirstlane(threadIdx.x) | blockIdx.x | blockIdx.y | blockIdx.z) == 0u;
+  }
+  __device__ __forceinline__ void tick(uint64_t t, bool mine) const {
+    if (mine && __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) == 0u) *next = t - off + add;
   }
 };
 
@@ -550,6 +558,7 @@ k_step(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, uint3
   const uint32_t site = (b - b0) * BLOCK + threadIdx.x;
   if (site >= L.nsites) return;
   const uint64_t t = ck.read();
+  const bool ticks = ck.ticks();
 
   float d[Q];
   Off o[Q];
@@ -584,7 +593,7 @@ k_step(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, uint3
       st<T, pol(CP::nt_store(plane))>(L, plane, o[i], C::enc(d[i]));
     });
   }
-  ck.tick(t);
+  ck.tick(t, ticks);
 }
 
 // ---------------------------------------------------------------- step kernel, row tiling
@@ -615,6 +624,7 @@ k_step_rows(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, 
   const uint32_t x = (bl - row * L.segs) * BLOCK + threadIdx.x;
   if (x >= L.nx) return;
   const uint64_t t = ck.read();
+  const bool ticks = ck.ticks();
   uint32_t z = 0, y = row;  // a 2D lattice has nz = 1
   if constexpr (M::D == 3) {
     z = fastdiv(row, L.dy_m, L.dy_s1, L.dy_s2);
@@ -692,7 +702,7 @@ k_step_rows(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, 
       else Raw<T>::template st<0>(plane_rsrc(L, j, ES), vx, C::enc(d[j]), ro * ES);
     }
   }
-  ck.tick(t);
+  ck.tick(t, ticks);
 }
 
 // ---------------------------------------------------------------- propagation only
@@ -719,6 +729,7 @@ k_propagate(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, 
   const uint32_t b0 = (nlat > 1) ? blk[l] : 0u;
   const uint32_t site = (b - b0) * BLOCK + threadIdx.x;
   if (site >= L.nsites) return;
+  const bool ticks = ck.ticks();
   Off o[Q];
   T h[Q];
   if (P == 0) {
@@ -739,7 +750,7 @@ k_propagate(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ blk, 
     constexpr int plane = P == 0 ? M::OPP[i] : i;
     st<T, pol(CP::nt_store(plane))>(L, plane, o[i], h[i]);
   });
-  if (ck.next) ck.tick(ck.read());
+  if (ticks) ck.tick(ck.read(), true);
 }
 
 template <class M, int S, int P, int BLOCK, bool RES>
@@ -759,6 +770,7 @@ k_propagate_rows(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ 
   const uint32_t row = fastdiv(bl, L.ds_m, L.ds_s1, L.ds_s2);
   const uint32_t x = (bl - row * L.segs) * BLOCK + threadIdx.x;
   if (x >= L.nx) return;
+  const bool ticks = ck.ticks();
   uint32_t z = 0, y = row;
   if constexpr (M::D == 3) {
     z = fastdiv(row, L.dy_m, L.dy_s1, L.dy_s2);
@@ -772,7 +784,7 @@ k_propagate_rows(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ 
     for (int i = 0; i < Q; ++i) h[i] = Raw<T>::template ld<EP>(plane_rsrc(L, i, ES), bx, r0 * ES);
 #pragma unroll
     for (int i = 0; i < Q; ++i) Raw<T>::template st<EP>(plane_rsrc(L, M::OPP[i], ES), bx, h[i], r0 * ES);
-    if (ck.next) ck.tick(ck.read());
+    if (ticks) ck.tick(ck.read(), true);
     return;
   }
   const uint32_t ym = (y == 0) ? L.wy : 0u - L.nx;
@@ -798,7 +810,7 @@ k_propagate_rows(const LatDesc* __restrict__ lats, const uint32_t* __restrict__ 
     if (CP::nt_store(j)) Raw<T>::template st<CPOL_NT>(plane_rsrc(L, j, ES), vx[j], h[j], ro[j] * ES);
     else Raw<T>::template st<0>(plane_rsrc(L, j, ES), vx[j], h[j], ro[j] * ES);
   }
-  if (ck.next) ck.tick(ck.read());
+  if (ticks) ck.tick(ck.read(), true);
 }
 
 // ---------------------------------------------------------------- fused passes

@@ -242,7 +242,7 @@ k_pass3d(const LatDesc* __restrict__ src, PassSide from, PassSide to, Clock ck, 
   };
   if (w < (uint32_t)P3_TY) walk(std::true_type{});
   else walk(std::false_type{});
-  ck.tick(t);
+  ck.tick(t, ck.ticks());
 }
 
 }  // namespace lbf

@@ -98,6 +98,7 @@ k_strip2d(const LatDesc* __restrict__ src, PassSide from, PassSide to, Clock ck,
   const uint32_t wave = xcd_remap(blockIdx.x, gridDim.x, 1) * W + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t wid = min(wave, g.ntx * g.nty - 1u);  // waves past the last strip walk it too and store nothing
   const uint64_t t = ck.read();
+  const bool ticks = ck.ticks();
   const uint32_t txi = wid % g.ntx, tyi = wid / g.ntx;
   const uint32_t x0 = txi * g.tx, y0 = tyi * g.len;
   const uint32_t TW = min(g.tx, nx - x0), YC = min(g.len, ny - y0);
@@ -199,7 +200,7 @@ k_strip2d(const LatDesc* __restrict__ src, PassSide from, PassSide to, Clock ck,
     for (int k = K - 1; k > 0; --k) yr[k] = yr[k - 1];
     yr[0] = yn;
   }
-  ck.tick(t);
+  ck.tick(t, ticks);
 }
 
 }  // namespace lbf
