@@ -432,14 +432,26 @@ uint32_t fused_chunk(uint64_t across, uint32_t extent, uint32_t slots) {
   return best;
 }
 
-// Rows a strip of the D2Q9 pass walks: as many strips as the device holds
-// waves at a time (slots), up to 64 rows (16384^2 fp32: 1.59 ms per step with
-// 32 rows, 1.57 with 64, 1.59 with 128, 1.62 with 256); shorter strips repeat
-// their halo rows more often than the waves they add are worth (2048^2 fp32:
-// 43.9 us per step with 4 rows, 34.0 with 16, 57.7 with 64).
-uint32_t strip_rows(uint32_t across, uint32_t extent, uint32_t slots) {
-  const uint64_t rows = ((uint64_t)across * extent + slots - 1u) / slots;
-  return (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, rows));
+// Rows a strip of the D2Q9 pass walks, of `across` strips, `extent` rows and
+// `slots` waves on the device at a time, up to 64 (16384^2 fp32: 1.59 ms per step
+// with 32 rows, 1.57 with 64, 1.59 with 128, 1.62 with 256).  A pass runs in
+// rounds of `slots` strips, each taking a strip's rows and its halo rows; where
+// the rounds are few, the length that minimises the estimate is taken, the
+// longest of equals (2048^2: 43.9 us per step with 4 rows, 34.0 with 16, 57.7 with
+// 64; 4000^2 bf16, 73 chunks in one round 108 us, 75 in one and a bit 124).
+// Chunks split the rows evenly, so that no strip walks rows that do not exist.
+uint32_t strip_rows(uint32_t across, uint32_t extent, uint32_t slots, uint32_t halo) {
+  auto chunks = [&](uint32_t len) { return (extent + len - 1u) / len; };
+  auto even = [&](uint32_t len) { return (extent + chunks(len) - 1u) / chunks(len); };
+  auto cost = [&](uint32_t len) {
+    return (((uint64_t)across * chunks(len) + slots - 1u) / slots) * (even(len) + 2u * halo);
+  };
+  const uint32_t longest = std::min(extent, 64u);
+  if ((uint64_t)across * chunks(longest) >= 8ull * slots) return even(longest);
+  uint32_t best = longest;
+  for (uint32_t len = longest; len > 0; --len)
+    if (cost(len) < cost(best)) best = len;
+  return even(best);
 }
 
 // Share of the sites of k_pass3d's tiles that lie in the box.
@@ -543,7 +555,10 @@ int plan_passes(lb_ctx* c) {
     // 85.5 to 73.6 us per step), below 200 MB, where they fill the chip too
     // unevenly, eight (2048^2, 151 MB, 39.0 to 35.3, with 16 37.9 to 39.4; 1700^2,
     // 104 MB, 22.8, with eight 23.2).
-    const bool wide = k == 2 && c->storage == LB_F32 && bytes > 140000000;
+    // Rows so few that a workgroup is mostly start and halo keep four strips
+    // (16 steps of 2000000 x 3, 216 MB, 910 us, with 16 strips 1064; 1000000 x 6
+    // 908 and 888; 4166666 x 1, 150 MB, 860, with eight 944; 1388888 x 3 620, 605).
+    const bool wide = k == 2 && c->storage == LB_F32 && bytes > 140000000 && L.ny >= (bytes > 200000000 ? 5u : 2u);
     const bool sync = wide || bytes > 320000000;
     const uint32_t waves = !wide ? S2_WAVES : bytes > 200000000 ? S2_WIDE_WAVES : S2_WIDE_WAVES / 2;
     p.threads = c->lattice == LB_D2Q9 ? 64 * (int)waves : P3_THREADS;
@@ -555,14 +570,17 @@ int plan_passes(lb_ctx* c) {
       const uint32_t w = 64u - 2u * (uint32_t)(k - 1);
       g.ntx = (L.nx + w - 1u) / w;
       g.tx = (L.nx + g.ntx - 1u) / g.ntx;
-      g.len = strip_rows(g.ntx, L.ny, slots * waves);
+      g.len = strip_rows(g.ntx, L.ny, slots * waves, (uint32_t)(k - 1));
       g.nty = (L.ny + g.len - 1u) / g.len;
       g.sync = sync;
       p.grid = dim3((g.ntx * g.nty + waves - 1u) / waves);
       // Strips of few rows spend more on the wider halo of four steps than
       // they save (1024^2 fp32, 4 rows: 14.2 us per step, with two 12.9;
-      // 2048^2, 15 rows: 34.0 and 37.9).
-      if (k == 4 && g.len >= 8) c->pass_max = 4;
+      // 2048^2, 15 rows: 34.0 and 37.9), in 16 bits up to longer ones, with noise
+      // above all (16 steps of 1728395 x 9 bf16 1958 us, with two 1655; 1037037 x
+      // 15 1775 and 1628; 518518 x 30 1669 and 1659).
+      const uint32_t four = c->storage == LB_F32 ? 8u : c->reps[0].kT > 0.0 ? 32u : 12u;
+      if (k == 4 && g.len >= four) c->pass_max = 4;
     } else {
       PassGeom& g = p.tiles;
       g.ntx = (L.nx + (uint32_t)P3_TX - 1u) / (uint32_t)P3_TX;
@@ -1013,19 +1031,21 @@ int default_schedule(lb_ctx* c) {
   // between 724^2 (19 MB, AA 6% faster) and 1024^2 (38 MB, fused 7% faster).
   // 16-bit D2Q9 state takes them above the resident band (16384^2 bf16: 1.55
   // against 1.84 ms per step; 4096^2, inside it, 111 against 118 us; 2048^2 36
-  // against 31).  So does 16-bit D3Q19 state without noise on boxes that fill the
+  // against 31), unless it has fewer than five rows (16 steps of 10000000 x 2
+  // bf16 2818 against 2270 us, 5000000 x 4 2310 and 2232, 3333333 x 6 2146 and
+  // 2341).  So does 16-bit D3Q19 state without noise on boxes that fill the
   // tiles (512^3 fp16 1.45 against 1.96 ms; 256^3 192 against 208 us; 400 x 300 x
   // 350, 86% filled, 636 against 655; 200 x 234 x 342, 76%, 8% slower); with
   // noise the collisions bound the pass (512^3 fp16 1.99 against 1.85 ms) and it
   // keeps one step per launch.
   const bool d2 = c->lattice == LB_D2Q9, f32 = c->storage == LB_F32;
   const uint64_t fused_above = f32 ? (d2 ? 32 * MIB : 256 * MIB) : 320 * MB;
-  const bool pays = d2 || f32 || (c->reps[0].kT == 0.0 && tile_fill(c->reps[0]) >= 0.9);
+  const bool pays = f32 || (d2 ? c->reps[0].ny >= 5 : c->reps[0].kT == 0.0 && tile_fill(c->reps[0]) >= 0.9);
   c->default_passes = c->d_small_b != nullptr;
   // 16-bit D2Q9 between the cache and that bound: passes too, unless a schedule
   // is set (4096 x 4099 fp16 108 against 119 us, bf16 111 against 119; 3001 x
   // 2777, 150 MB, 58.4 and 58.6).
-  const bool beyond_cache = d2 && !f32 && total > 256 * MIB;
+  const bool beyond_cache = d2 && !f32 && pays && total > 256 * MIB;
   if (fused_eligible(c) && ((pays && total > fused_above) || beyond_cache)) {
     const std::string keep = g_last_error;
     size_t free_b = 0, total_b = 0;

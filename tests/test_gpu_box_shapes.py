@@ -1,0 +1,72 @@
+"""Wide, short, flat and thin boxes, where the halo of a pass weighs most: the
+passes that such a box takes give the bits of AA steps, and its default
+schedule is not slower than AA steps (which are timed beside it)."""
+import pytest
+import torch
+
+import paper_0707_1581_amd as lbf
+from tests.gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+# The boxes timed here took 1.3 to 13 times an AA step before their passes were
+# fitted to them, and take 0.6 to 1.05 times one since.
+LIMIT = 1.2
+
+
+def _lat(lattice, dims, storage, kT=1e-4):
+    return lbf.Lattice(*dims, rho0=1.0, kT=kT, gamma_bulk=0.5, gamma_shear=0.8, gamma_odd=-0.3, gamma_even=0.2,
+                       seed=77, lattice=lattice, storage=storage, init="thermal")
+
+
+def _ms(lat, steps=16, reps=7):
+    best = float("inf")
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for _ in range(reps):
+        ev[0].record()
+        lat.step(steps)
+        ev[1].record()
+        torch.cuda.synchronize()
+        best = min(best, ev[0].elapsed_time(ev[1]))
+    return best
+
+
+def _not_slower(lattice, dims, storage, **sched):
+    lats = [_lat(lattice, dims, storage) for _ in range(2)]
+    lats[0].set_schedule(fused=0)
+    if sched:
+        lats[1].set_schedule(**sched)
+    aa, here = (_ms(lat) for lat in lats)
+    say(f"{lattice} {dims} {storage}: {1e3 * here:.0f} us, AA {1e3 * aa:.0f} us")
+    assert here <= LIMIT * aa, (dims, here, aa)
+    for lat in lats:
+        lat.close()
+
+
+def _same_bits(lattice, dims, storage, fused, steps):
+    lats = [_lat(lattice, dims, storage) for _ in range(2)]
+    lats[0].set_schedule(fused=0)
+    if fused is not None:
+        lats[1].set_schedule(fused=fused)
+    for n in steps:
+        for lat in lats:
+            lat.step(n)
+        assert torch.equal(lats[0].state, lats[1].state), (dims, storage, n)
+    for lat in lats:
+        lat.close()
+
+
+# ---------------------------------------------------------------- D2Q9 strips
+@pytest.mark.parametrize("dims,storage", [((2000000, 3, 1), "f32"), ((4000000, 8, 1), "f32"),
+                                          ((2000000, 20, 1), "f32"), ((5000000, 4, 1), "bf16")])
+def test_short_strips_not_slower(dims, storage):
+    _not_slower("d2q9", dims, storage)
+
+
+@pytest.mark.parametrize("storage,dims", [("f32", (1500001, 4, 1)), ("f32", (1300001, 5, 1)), ("f32", (4000003, 1, 1)),
+                                          ("f32", (300001, 30, 1)), ("bf16", (120001, 130, 1)),
+                                          ("f16", (500009, 33, 1))])
+def test_short_strips_keep_the_bits(storage, dims):
+    """Strips of the whole height and chunks that split it evenly, with and
+    without the strips of a workgroup in step."""
+    _same_bits("d2q9", dims, storage, 1, (4, 7, 8, 18))
