@@ -242,8 +242,10 @@ void* pass_ptr(int lattice, int storage, int k, int threads, bool pull, bool own
 // Fused passes of small lattices, by the lanes of a workgroup.
 template <class M, int S, bool PROP>
 void* block_ptr_s(int lanes) {
-  return lanes <= 256 ? (void*)&k_block<M, S, PROP, 256>
-                      : lanes <= 512 ? (void*)&k_block<M, S, PROP, 512> : (void*)&k_block<M, S, PROP, 1024>;
+  if constexpr (M::D == 2) {
+    if (lanes > 512) return (void*)&k_block<M, S, PROP, 1024>;
+  }
+  return lanes <= 256 ? (void*)&k_block<M, S, PROP, 256> : (void*)&k_block<M, S, PROP, 512>;
 }
 template <class M, bool PROP>
 void* block_ptr_m(int storage, int lanes) {
@@ -460,29 +462,6 @@ double tile_fill(const lb_params& p) {
   return (double)p.nx * p.ny / (tiled(p.nx, P3_TX) * tiled(p.ny, P3_TY));
 }
 
-// Whether the passes over a lattice are k_block's: D2Q9 of up to 64 MB (1024^2
-// fp32, 38 MB: 10.6 us per step, strips 11.7; 2048^2: 34.3 and 32.8) and D3Q19
-// of up to 16384 sites (beyond, the AA steps are as fast: 24^3 fp32 4.0 against
-// 4.3 us, 32^3 5.6 against 4.6).
-bool block_passes(const lb_params& p) {
-  if (p.lattice == LB_D2Q9) return sites_of(p) * D2Q9::Q * elem_size(p.storage) <= 64000000ull;
-  return sites_of(p) <= 16384;
-}
-
-// Bytes of the second buffer of a small lattice, which takes several steps per
-// launch (k_block) by default: D3Q19 of up to 16384 sites (16^3 fp32 3.2 us per
-// step, AA 3.9), D2Q9 of up to 32 MiB in fp32 (64 x 48 1.75 against 3.5 us,
-// 512^2 4.4 against 5.5, 724^2 6.5 against 8.4; beyond, the schedule is fused)
-// and 5 MB in 16 bits (512^2 bf16 4.7 against 4.8; 1024^2 11.4 against 11.3).  0
-// for a larger lattice or a batch.
-size_t small_bytes(const lb_ctx* c) {
-  if (c->reps.size() != 1) return 0;
-  const lb_params& p = c->reps[0];
-  const size_t bytes = (size_t)q_of(p.lattice) * sites_of(p) * elem_size(p.storage);
-  if (p.lattice == LB_D2Q9) return bytes <= (p.storage == LB_F32 ? 32u << 20 : 5000000u) ? bytes : 0;
-  return block_passes(p) ? bytes : 0;
-}
-
 // Blocks of k_block and the most steps a pass of them takes.  D2Q9: 58 x 10
 // sites (one wave a row at four steps) where that makes 128 workgroups or more
 // (256^2 fp32 2.9 us per step, with 8 x 8 3.5; 1024^2 10.6 and 19.2), else 16 x
@@ -491,27 +470,95 @@ size_t small_bytes(const lb_ctx* c) {
 // eight steps a pass (1.75).  D3Q19: 4^3 and three steps (16^3 fp32 3.2 us, with
 // two steps 3.6, 8 x 8 x 4 and two 4.1; AA 3.9).  Blocks split the lattice
 // evenly.
+struct BlockShape {
+  uint32_t b[3];      // sites of a block
+  uint32_t most;      // steps of a pass
+  uint32_t n[3];      // blocks
+  uint32_t lanes(uint32_t steps, bool d2) const {  // at most 64 x 16, 22 x 22 (8 x 8, eight steps), 8^3
+    const uint32_t h = 2u * (steps - 1u);
+    return (b[0] + h) * (b[1] + h) * (d2 ? 1u : b[2] + h);
+  }
+  uint64_t waves(bool d2) const {
+    return (uint64_t)n[0] * n[1] * n[2] * ((lanes(most, d2) + 63u) / 64u);
+  }
+};
+BlockShape block_shape(const lb_params& p) {
+  const bool d2 = p.lattice == LB_D2Q9;
+  const uint32_t box[3] = {(uint32_t)p.nx, (uint32_t)p.ny, (uint32_t)p.nz};
+  auto blocks = [](uint32_t n, uint32_t b) { return (n + b - 1u) / b; };
+  BlockShape s{{4, 4, 4}, 3, {}};
+  if (d2) {
+    constexpr uint32_t SIZES[3][2] = {{58, 10}, {16, 16}, {8, 8}};
+    uint64_t count = 0;
+    s.b[2] = 1;
+    for (const auto& sz : SIZES) {
+      s.b[0] = sz[0];
+      s.b[1] = sz[1];
+      count = (uint64_t)blocks(box[0], s.b[0]) * blocks(box[1], s.b[1]);
+      if (count >= 128) break;
+    }
+    s.most = count <= 64 ? 8 : 4;
+  }
+  for (int a = 0; a < 3; ++a) {
+    s.n[a] = blocks(box[a], s.b[a]);
+    s.b[a] = blocks(box[a], s.n[a]);
+  }
+  return s;
+}
+
+// Lanes that one step of two in k_strip2d collides per site of the lattice.
+double strip_lanes(const lb_params& p) {
+  const uint32_t across = ((uint32_t)p.nx + 61u) / 62u, slots = 8192;  // waves of 256 CUs
+  const uint32_t len = strip_rows(across, (uint32_t)p.ny, slots, 1);
+  return 64.0 * across / p.nx * (len + 2u) / len;
+}
+
+// Whether the passes over a lattice are k_block's: D2Q9 of up to 64 MB (1024^2
+// fp32, 38 MB: 10.6 us per step, strips 11.7; 2048^2: 34.3 and 32.8) and D3Q19
+// of up to 16384 sites, unless the halo of a flat or thin box weighs more than
+// in the passes of larger lattices.  D2Q9: a block collides 1.3 times the lanes
+// of a strip (16 steps of 1250000 x 1 fp32 558 us in blocks, 282 in strips;
+// 246031 x 7 330 and 274; at 1.14 times, 172222 x 10, 231 and 291); below a
+// million sites 2.3 times, a lattice of one row (416666 x 1 203 and 130; two
+// rows 127 and 133).  D3Q19: 24 lanes or more per site of one plane (16384 x 1 x
+// 1 153 us, k_pass3d 75; 4000 x 4 x 1, 20 lanes, 83 and 89).
+bool block_passes(const lb_params& p) {
+  const uint64_t sites = sites_of(p);
+  const bool d2 = p.lattice == LB_D2Q9;
+  if (d2 ? sites * D2Q9::Q * elem_size(p.storage) > 64000000ull : sites > 16384) return false;
+  const uint64_t waves = block_shape(p).waves(d2);
+  const double lanes = 64.0 * (double)waves / (double)sites;
+  if (d2) return sites < 400000 || lanes <= (sites < 1000000 ? 2.3 : 1.3) * strip_lanes(p);
+  return p.nz > 1 || waves <= 4096 || lanes < 24.0;
+}
+
+// Bytes of the second buffer of a small lattice, which takes several steps per
+// launch (k_block) by default: D3Q19 of up to 16384 sites (16^3 fp32 3.2 us per
+// step, AA 3.9; beyond, the AA steps are as fast: 24^3 fp32 4.0 against 4.3 us,
+// 32^3 5.6 against 4.6), D2Q9 of up to 32 MiB in fp32 (64 x 48 1.75 against 3.5
+// us, 512^2 4.4 against 5.5, 724^2 6.5 against 8.4; beyond, the schedule is
+// fused) and 5 MB in 16 bits (512^2 bf16 4.7 against 4.8; 1024^2 11.4 against
+// 11.3).  Flat and thin boxes, whose blocks are mostly halo, keep AA steps where
+// the blocks are more waves than run at a time (16 steps of 128 x 128 x 1 fp32,
+// 5120 waves: 84 us in blocks, AA 65; 64 x 64 x 4, 2048 waves: 62 and 65; D2Q9
+// of one row: 138888 x 1, 16766 waves, 87 and 72, 16384 x 1, 1981 waves, 32 and
+// 55).  0 for those, for a larger lattice or a batch.
+size_t small_bytes(const lb_ctx* c) {
+  if (c->reps.size() != 1 || !block_passes(c->reps[0])) return 0;
+  const lb_params& p = c->reps[0];
+  const bool d2 = p.lattice == LB_D2Q9;
+  const size_t bytes = (size_t)q_of(p.lattice) * sites_of(p) * elem_size(p.storage);
+  if (d2 && bytes > (p.storage == LB_F32 ? 32u << 20 : 5000000u)) return 0;
+  const uint64_t waves = block_shape(p).waves(d2);
+  const bool resident = waves <= (d2 ? 8192u : 4096u);
+  return resident || (d2 && 64 * waves <= 5 * sites_of(p)) ? bytes : 0;
+}
+
 void plan_blocks(lb_ctx* c) {
   const LatDesc& L = c->lats[0];
   const bool d2 = c->lattice == LB_D2Q9;
-  auto blocks = [](uint32_t n, uint32_t b) { return (n + b - 1u) / b; };
-  uint32_t b[3] = {4, 4, 4};
-  c->pass_max = 3;
-  if (d2) {
-    constexpr uint32_t SIZES[3][2] = {{58, 10}, {16, 16}, {8, 8}};
-    uint32_t count = 0;
-    b[2] = 1;
-    for (const auto& sz : SIZES) {
-      b[0] = sz[0];
-      b[1] = sz[1];
-      count = blocks(L.nx, b[0]) * blocks(L.ny, b[1]);
-      if (count >= 128) break;
-    }
-    c->pass_max = count <= 64 ? 8 : 4;
-  }
-  b[0] = blocks(L.nx, blocks(L.nx, b[0]));
-  b[1] = blocks(L.ny, blocks(L.ny, b[1]));
-  b[2] = blocks(L.nz, blocks(L.nz, b[2]));
+  const BlockShape s = block_shape(c->reps[0]);
+  c->pass_max = (int)s.most;
   for (int k = 2; k <= c->pass_max; ++k) {
     lb_ctx::PassPlan& p = c->plans[k];
     BlockGeom& g = p.block;
@@ -519,17 +566,16 @@ void plan_blocks(lb_ctx* c) {
     g.nx = L.nx;
     g.ny = L.ny;
     g.nz = L.nz;
-    g.bx = b[0];
-    g.by = b[1];
-    g.bz = b[2];
-    g.rx = b[0] + h;
-    g.rxy = g.rx * (b[1] + h);
+    g.bx = s.b[0];
+    g.by = s.b[1];
+    g.bz = s.b[2];
+    g.rx = s.b[0] + h;
+    g.rxy = g.rx * (s.b[1] + h);
     g.mx = ((1u << 20) + g.rx - 1u) / g.rx;
     g.mxy = ((1u << 20) + g.rxy - 1u) / g.rxy;
     g.steps = (uint32_t)k;
-    const uint32_t lanes = g.rxy * (d2 ? 1u : b[2] + h);  // at most 64 x 16, 22 x 22 (8 x 8, eight steps), 8^3
-    p.threads = (int)((lanes + 63u) / 64u * 64u);
-    p.grid = dim3(blocks(L.nx, b[0]), blocks(L.ny, b[1]), blocks(L.nz, b[2]));
+    p.threads = (int)((s.lanes((uint32_t)k, d2) + 63u) / 64u * 64u);
+    p.grid = dim3(s.n[0], s.n[1], s.n[2]);
   }
 }
 
@@ -1033,14 +1079,16 @@ int default_schedule(lb_ctx* c) {
   // against 1.84 ms per step; 4096^2, inside it, 111 against 118 us; 2048^2 36
   // against 31), unless it has fewer than five rows (16 steps of 10000000 x 2
   // bf16 2818 against 2270 us, 5000000 x 4 2310 and 2232, 3333333 x 6 2146 and
-  // 2341).  So does 16-bit D3Q19 state without noise on boxes that fill the
+  // 2341); fp32 of one row keeps AA steps too (1250000 x 1 339 and 288,
+  // 2000000 x 1 414 and 387).  So does 16-bit D3Q19 state without noise on boxes that fill the
   // tiles (512^3 fp16 1.45 against 1.96 ms; 256^3 192 against 208 us; 400 x 300 x
   // 350, 86% filled, 636 against 655; 200 x 234 x 342, 76%, 8% slower); with
   // noise the collisions bound the pass (512^3 fp16 1.99 against 1.85 ms) and it
   // keeps one step per launch.
   const bool d2 = c->lattice == LB_D2Q9, f32 = c->storage == LB_F32;
   const uint64_t fused_above = f32 ? (d2 ? 32 * MIB : 256 * MIB) : 320 * MB;
-  const bool pays = f32 || (d2 ? c->reps[0].ny >= 5 : c->reps[0].kT == 0.0 && tile_fill(c->reps[0]) >= 0.9);
+  const bool pays = d2 ? c->reps[0].ny >= (f32 ? 2 : 5)
+                       : f32 || (c->reps[0].kT == 0.0 && tile_fill(c->reps[0]) >= 0.9);
   c->default_passes = c->d_small_b != nullptr;
   // 16-bit D2Q9 between the cache and that bound: passes too, unless a schedule
   // is set (4096 x 4099 fp16 108 against 119 us, bf16 111 against 119; 3001 x

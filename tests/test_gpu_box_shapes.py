@@ -70,3 +70,24 @@ def test_short_strips_keep_the_bits(storage, dims):
     """Strips of the whole height and chunks that split it evenly, with and
     without the strips of a workgroup in step."""
     _same_bits("d2q9", dims, storage, 1, (4, 7, 8, 18))
+
+
+# ---------------------------------------------------------------- blocks of small lattices
+@pytest.mark.parametrize("lattice,dims,storage", [("d3q19", (16384, 1, 1), "f32"), ("d3q19", (8000, 2, 1), "f16"),
+                                                  ("d3q19", (128, 128, 1), "f32"), ("d3q19", (5400, 1, 3), "f32"),
+                                                  ("d2q9", (1250000, 1, 1), "f32"), ("d2q9", (416666, 1, 1), "f32"),
+                                                  ("d2q9", (222222, 1, 1), "bf16")])
+def test_flat_boxes_not_slower(lattice, dims, storage):
+    _not_slower(lattice, dims, storage)
+
+
+@pytest.mark.parametrize("lattice,dims", [("d3q19", (16384, 1, 1)), ("d3q19", (5401, 3, 1)), ("d3q19", (4000, 4, 1)),
+                                          ("d3q19", (128, 128, 1)), ("d3q19", (4000, 1, 1)),
+                                          ("d2q9", (1000003, 1, 1)), ("d2q9", (250007, 5, 1)),
+                                          ("d2q9", (100003, 10, 1)), ("d2q9", (416669, 1, 1)),
+                                          ("d2q9", (80021, 1, 1))])
+@pytest.mark.parametrize("fused", [None, 1])
+def test_flat_boxes_keep_the_bits(lattice, dims, fused):
+    """Either side of each line between blocks, passes of larger lattices and
+    AA steps."""
+    _same_bits(lattice, dims, "f32", fused, (4, 7, 12))
