@@ -607,7 +607,8 @@ int plan_passes(lb_ctx* c) {
     const bool wide = k == 2 && c->storage == LB_F32 && bytes > 140000000 && L.ny >= (bytes > 200000000 ? 5u : 2u);
     const bool sync = wide || bytes > 320000000;
     const uint32_t waves = !wide ? S2_WAVES : bytes > 200000000 ? S2_WIDE_WAVES : S2_WIDE_WAVES / 2;
-    p.threads = c->lattice == LB_D2Q9 ? 64 * (int)waves : P3_THREADS;
+    const uint32_t nty = (L.ny + P3_TY - 1u) / P3_TY, ty = (L.ny + nty - 1u) / nty;  // D3Q19: tiles along y, their rows
+    p.threads = 64 * (int)(c->lattice == LB_D2Q9 ? waves : ty + 3u);
     int per_cu = 0;
     HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pass_ptr(c->lattice, c->storage, k, p.threads, true, true, true, false), p.threads, 0));
     const uint32_t slots = (uint32_t)std::max(1, cus * per_cu);  // workgroups resident at a time
@@ -630,9 +631,9 @@ int plan_passes(lb_ctx* c) {
     } else {
       PassGeom& g = p.tiles;
       g.ntx = (L.nx + (uint32_t)P3_TX - 1u) / (uint32_t)P3_TX;
-      g.nty = (L.ny + (uint32_t)P3_TY - 1u) / (uint32_t)P3_TY;
+      g.nty = nty;
       g.tx = P3_TX;
-      g.ty = P3_TY;
+      g.ty = ty;
       g.len = fused_chunk((uint64_t)g.ntx * g.nty, L.nz, slots);
       p.grid = dim3(g.ntx * g.nty * ((L.nz + g.len - 1u) / g.len));
     }

@@ -3,10 +3,13 @@
 // k_pass3d advances a D3Q19 lattice from even t by two steps in one pass over
 // memory, from one buffer to another.
 //
-// Work split.  A workgroup of 16 waves owns a 64 x 13 column of x-y sites and
-// walks a chunk of planes along z.  Thirteen waves hold one x-row each, two
+// Work split.  A workgroup of up to 16 waves owns a column of 64 x-y sites by up
+// to 13 rows and walks a chunk of planes along z.  One wave holds each x-row, two
 // the halo rows and one the halo columns (periodic; ragged tiles leave lanes
-// idle).  In each phase every wave collides the first step of its sites of the
+// idle).  Tiles split the rows of the box evenly and the workgroup has as many
+// waves as its tile needs: a wave without a row of its own would load and collide
+// all the same (512 x 7 x 1200 fp32, 16 steps, 1744 to 1309 us; 512 x 14 x 600
+// 1907 to 1341; 512 x 40 x 300 2120 to 1795).  In each phase every wave collides the first step of its sites of the
 // next plane u and writes the populations that move in x or y to LDS; after
 // one barrier the row waves pull what arrives at their sites and collide the
 // second step of plane u - 1: its down-going populations have just come from u,
@@ -49,8 +52,8 @@
 
 namespace lbf {
 
-constexpr int P3_TX = 64, P3_TY = 13;                // interior sites of a tile
-constexpr int P3_THREADS = (P3_TY + 3) * 64;         // row, halo-row and halo-column waves
+constexpr int P3_TX = 64, P3_TY = 13;                // most interior sites of a tile
+constexpr int P3_THREADS = (P3_TY + 3) * 64;         // its row, halo-row and halo-column waves
 constexpr int P3_ROW = P3_TX + 2;                    // LDS row: the tile's with its halo
 constexpr int P3_PLANE = P3_ROW * (P3_TY + 2);       // LDS values of one population
 constexpr int P3_XCH = 16;                           // populations that move in x or y
@@ -72,7 +75,8 @@ struct P3Slot {
   }
 };
 
-// Tiles along x and y, the rows of a tile, and the planes of a chunk.
+// Tiles along x and y, the sites of a tile (a workgroup has ty + 3 waves), and
+// the planes of a chunk.
 struct PassGeom {
   uint32_t ntx, nty, tx, ty, len;
 };
@@ -106,9 +110,9 @@ k_pass3d(const LatDesc* __restrict__ src, PassSide from, PassSide to, Clock ck, 
   // this lane's site in tile coordinates plus one, 0..TW + 1 and 0..TH + 1;
   // idle lanes repeat one at the far edge
   uint32_t lx = lane + 1u, ly = w + 1u;
-  if (w == (uint32_t)P3_TY) ly = 0u;
-  else if (w == (uint32_t)P3_TY + 1u) ly = TH + 1u;
-  else if (w > (uint32_t)P3_TY + 1u) {
+  if (w == g.ty) ly = 0u;
+  else if (w == g.ty + 1u) ly = TH + 1u;
+  else if (w > g.ty + 1u) {
     lx = lane < 32u ? 0u : TW + 1u;
     ly = lane & 31u;
   }
@@ -240,7 +244,7 @@ k_pass3d(const LatDesc* __restrict__ src, PassSide from, PassSide to, Clock ck, 
       zc = zn;
     }
   };
-  if (w < (uint32_t)P3_TY) walk(std::true_type{});
+  if (w < g.ty) walk(std::true_type{});
   else walk(std::false_type{});
   ck.tick(t, ck.ticks());
 }

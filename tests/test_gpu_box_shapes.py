@@ -91,3 +91,17 @@ def test_flat_boxes_keep_the_bits(lattice, dims, fused):
     """Either side of each line between blocks, passes of larger lattices and
     AA steps."""
     _same_bits(lattice, dims, "f32", fused, (4, 7, 12))
+
+
+# ---------------------------------------------------------------- D3Q19 tiles
+@pytest.mark.parametrize("dims", [(512, 5, 1500), (512, 14, 600)])
+def test_tiles_of_few_rows_not_slower(dims):
+    _not_slower("d3q19", dims, "f32")
+
+
+@pytest.mark.parametrize("dims", [(70, 1, 260), (65, 2, 140), (130, 5, 40), (66, 14, 30), (64, 27, 11), (63, 40, 9),
+                                  (67, 157, 4)])
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+def test_tiles_of_few_rows_keep_the_bits(dims, storage):
+    """Workgroups of 4 to 16 waves; a last tile of fewer rows than the others."""
+    _same_bits("d3q19", dims, storage, 1, (4, 7, 8))
