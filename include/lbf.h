@@ -134,17 +134,22 @@ size_t lb_state_bytes(const lb_params* p);
  * Enqueues the initial state (init_kind) as the state at step count t0
  * (t0 >= 0); d_fields is required for LB_INIT_FIELDS and ignored otherwise.
  * The context stores p by value.  Its default schedule (lb_get_schedule)
- * depends on the state: an fp32 lattice of more than 256 MiB (D3Q19) or
- * 32 MiB (D2Q9), or a 16-bit one of more than 320 MB that is D2Q9 or has
- * kT = 0, takes the fused schedule when the device has room for its second
- * state buffer (16 bits: when that is at most a quarter of the free memory)
- * and its z-planes, or D2Q9 rows, hold less than 4 GiB per population; lb_init
- * then allocates the buffer (release it with lb_set_schedule and fused = 0).
+ * depends on the state.  It is the fused schedule for an fp32 lattice of more
+ * than 256 MiB (D3Q19), or of more than 32 MiB and two rows or more (D2Q9); and
+ * for a 16-bit one of more than 320 MB that has five rows or more (D2Q9), or
+ * kT = 0 and a box that fills 85% of tiles of 64 x 13 sites (D3Q19: nx fills
+ * whole multiples of 64, ny, split evenly, rows of up to 13); provided that the
+ * device has room for its second state buffer (16 bits: when that is at most a
+ * quarter of the free memory) and that its z-planes, or D2Q9 rows, hold less than
+ * 4 GiB per population.  lb_init then allocates the buffer (release it with
+ * lb_set_schedule and fused = 0).
  * Small lattices (D3Q19 of up to 16384 sites, D2Q9 of up to 32 MiB in fp32 or
- * 5 MB in 16 bits), and 16-bit D2Q9 ones of 256 MiB to 320 MB, report
+ * 5 MB in 16 bits; not the flat and thin ones that the halo of such steps slows
+ * down), and 16-bit D2Q9 ones of 256 MiB to 320 MB and five rows or more, report
  * fused = 0 and, until lb_set_schedule or lb_autotune, advance by several
  * steps per launch all the same where there is room, through a buffer of that
- * size which belongs to the context.  With LB_BF16 storage and kT = 0 it
+ * size which belongs to the context; setting the schedule that
+ * lb_get_schedule reports ends that.  With LB_BF16 storage and kT = 0 it
  * succeeds and leaves a warning in lb_last_error(). */
 int lb_init(const lb_params* p, void* d_state, void* hip_stream, int32_t init_kind,
             const float* d_fields, int64_t t0, lb_ctx** out);

@@ -456,10 +456,11 @@ uint32_t strip_rows(uint32_t across, uint32_t extent, uint32_t slots, uint32_t h
   return even(best);
 }
 
-// Share of the sites of k_pass3d's tiles that lie in the box.
+// Share of the sites of k_pass3d's tiles that lie in the box (the tiles split
+// the rows evenly, see plan_passes).
 double tile_fill(const lb_params& p) {
-  auto tiled = [](int32_t n, int t) { return (double)((n + t - 1) / t * t); };
-  return (double)p.nx * p.ny / (tiled(p.nx, P3_TX) * tiled(p.ny, P3_TY));
+  const int tx = (p.nx + P3_TX - 1) / P3_TX, ty = (p.ny + P3_TY - 1) / P3_TY;
+  return (double)p.nx * p.ny / ((double)tx * P3_TX * ty * ((p.ny + ty - 1) / ty));
 }
 
 // Blocks of k_block and the most steps a pass of them takes.  D2Q9: 58 x 10
@@ -1070,26 +1071,28 @@ int default_schedule(lb_ctx* c) {
       c->sched.group_mb = 224;
     }
   }
-  // State beyond the cache streams through HBM: passes of two (D3Q19) or four
-  // (D2Q9) fused steps per launch move a fraction of the bytes, when the
+  // State beyond the cache streams through HBM: passes of two (D3Q19) or two to
+  // four (D2Q9) fused steps per launch move a fraction of the bytes, when the
   // second buffer fits on the device; planes of 4 GiB or more included.
-  // Measured crossovers of fp32 against the resident AA steps: D3Q19 between
-  // 152^3 (267 MB, AA 8% faster) and 156^3 (289 MB, fused 13% faster), D2Q9
-  // between 724^2 (19 MB, AA 6% faster) and 1024^2 (38 MB, fused 7% faster).
+  // fp32: D3Q19 crosses the resident AA steps between 152^3 (267 MB, 16 steps 1285
+  // us against 1346 in passes) and 156^3 (289 MB, 1582 and 1428).  D2Q9 passes are
+  // the faster ones at every size (724^2, 19 MB, 6.5 against 8.4 us per step;
+  // 1024^2 10.6 and 13); from 32 MiB on the schedule says so.  One row keeps AA
+  // steps: a strip of it collides three (1250000 x 1 339 and 288, 2000000 x 1 414
+  // and 387 us).
   // 16-bit D2Q9 state takes them above the resident band (16384^2 bf16: 1.55
   // against 1.84 ms per step; 4096^2, inside it, 111 against 118 us; 2048^2 36
   // against 31), unless it has fewer than five rows (16 steps of 10000000 x 2
   // bf16 2818 against 2270 us, 5000000 x 4 2310 and 2232, 3333333 x 6 2146 and
-  // 2341); fp32 of one row keeps AA steps too (1250000 x 1 339 and 288,
-  // 2000000 x 1 414 and 387).  So does 16-bit D3Q19 state without noise on boxes that fill the
-  // tiles (512^3 fp16 1.45 against 1.96 ms; 256^3 192 against 208 us; 400 x 300 x
-  // 350, 86% filled, 636 against 655; 200 x 234 x 342, 76%, 8% slower); with
-  // noise the collisions bound the pass (512^3 fp16 1.99 against 1.85 ms) and it
-  // keeps one step per launch.
+  // 2341).  So does 16-bit D3Q19 state without noise on boxes that fill 85% of the
+  // tiles (512^3 fp16 1.45 against 1.96 ms; 400 x 300 x 350, 86% filled, 568
+  // against 615 us; 230^3, 88%, 177 and 196; 200 x 300 x 300, 75%, 279 and 259);
+  // with noise the collisions bound the pass (512^3 fp16 1.99 against 1.85 ms) and
+  // it keeps one step per launch.
   const bool d2 = c->lattice == LB_D2Q9, f32 = c->storage == LB_F32;
   const uint64_t fused_above = f32 ? (d2 ? 32 * MIB : 256 * MIB) : 320 * MB;
   const bool pays = d2 ? c->reps[0].ny >= (f32 ? 2 : 5)
-                       : f32 || (c->reps[0].kT == 0.0 && tile_fill(c->reps[0]) >= 0.9);
+                       : f32 || (c->reps[0].kT == 0.0 && tile_fill(c->reps[0]) >= 0.85);
   c->default_passes = c->d_small_b != nullptr;
   // 16-bit D2Q9 between the cache and that bound: passes too, unless a schedule
   // is set (4096 x 4099 fp16 108 against 119 us, bf16 111 against 119; 3001 x

@@ -105,3 +105,19 @@ def test_tiles_of_few_rows_not_slower(dims):
 def test_tiles_of_few_rows_keep_the_bits(dims, storage):
     """Workgroups of 4 to 16 waves; a last tile of fewer rows than the others."""
     _same_bits("d3q19", dims, storage, 1, (4, 7, 8))
+
+
+@pytest.mark.parametrize("dims,fused", [((400, 300, 350), 1), ((200, 300, 300), 0)])
+def test_noiseless_passes_from_the_measured_fill(dims, fused):
+    """16-bit boxes without noise take the passes from 85% of their tiles on:
+    86% (passes 8% faster) and 75% (passes 8% slower)."""
+    lats = [_lat("d3q19", dims, "f16", kT=1e-4)]
+    lats += [lbf.Lattice(*dims, kT=0.0, gamma_shear=0.5, storage="f16", init="keep", state=lats[0].state.clone())
+             for _ in range(2)]
+    assert lats[1].schedule()["fused"] == fused
+    lats[2].set_schedule(fused=0)
+    for lat in lats[1:]:
+        lat.step(9)
+    assert torch.equal(lats[1].state, lats[2].state)
+    for lat in lats:
+        lat.close()
