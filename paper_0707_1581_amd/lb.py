@@ -174,6 +174,20 @@ def _stream_ptr(device, stream):
     return ctypes.c_void_p(s.cuda_stream), s
 
 
+# handle of a device's current stream: a torch.cuda.Stream for it takes as long
+# as a gather of a small lattice (None: this torch does not have the call)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _is_current(stream, device):
+    """Whether stream is the caller's current stream of device.  Streams of two
+    devices may have one handle (the default streams do), so both count."""
+    if _raw_stream is None:
+        return stream == torch.cuda.current_stream(device)
+    index = device.index if device.index is not None else torch.cuda.current_device()
+    return stream.device_index == index and stream.cuda_stream == _raw_stream(index)
+
+
 def _adopt(t, device, lat_stream):
     """Order the library's work on lat_stream after the caller's current
     stream (which may have just produced or recycled t's memory), and keep
@@ -210,11 +224,7 @@ class _Gathers:
         caller's current stream may use at once."""
         lat_stream = self.stream if isinstance(self, Lattice) else self._ens.stream
         out = torch.empty((rows, *self._dims()), dtype=torch.float32, device=self.device)
-        # the handles alone are compared (a torch.cuda.Stream for the current
-        # stream takes as long as a gather of a small lattice); the streams
-        # are ordered as by _adopt where they differ
-        index = self.device.index if self.device.index is not None else torch.cuda.current_device()
-        other = torch._C._cuda_getCurrentRawStream(index) != lat_stream.cuda_stream
+        other = not _is_current(lat_stream, self.device)
         if other:
             _adopt(out, self.device, lat_stream)
         rc = fn(self._ctx, _aligned(out))
@@ -309,8 +319,11 @@ class Lattice(_Gathers):
         """xcd_remap and tiling: an int for both step parities or an
         (even, odd) pair; resident: cache every access (1) or stream (0);
         group_mb: replica groups of at most this many MiB of state (0: one);
-        fused: two steps per launch through a second buffer (1) or one
-        in-place step per launch (0)."""
+        fused: two to eight steps per launch through a second buffer (1) or one
+        in-place step per launch (0).  A lattice that took several steps per
+        launch before any schedule was set (small ones, and 16-bit D2Q9 ones of
+        256 to 320 MB, which report fused = 0) takes one from then on, also when
+        the schedule set is the one that schedule() reports."""
         s = _make_schedule(block, order, xcd_remap, graph_chunk, tiling, resident, group_mb, fused)
         _check(lib().lb_set_schedule(self._ctx, ctypes.byref(s)), "lb_set_schedule")
 
@@ -419,8 +432,7 @@ class Ensemble:
         """xcd_remap and tiling: an int for both step parities or an
         (even, odd) pair; resident: cache every access (1) or stream (0);
         group_mb: replica groups of at most this many MiB of state (0: one);
-        fused: two steps per launch through a second buffer (1) or one
-        in-place step per launch (0)."""
+        fused: 0 (an ensemble takes one in-place step per launch)."""
         s = _make_schedule(block, order, xcd_remap, graph_chunk, tiling, resident, group_mb, fused)
         _check(lib().lb_set_schedule(self._ctx, ctypes.byref(s)), "lb_set_schedule")
 
