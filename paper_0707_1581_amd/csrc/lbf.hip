@@ -368,6 +368,7 @@ struct lb_ctx {
   // fused schedule: the second state buffer (library-owned), the launches of
   // its passes and the most steps a pass takes
   char* d_state_b = nullptr;
+  size_t pitch_b = 0;            // bytes from one x-row of it to the next
   struct PassPlan {
     PassGeom tiles{};   // D3Q19
     StripGeom strip{};  // D2Q9
@@ -710,36 +711,44 @@ bool fused_eligible(const lb_ctx* c) {
 // The fused schedule's second buffer holds the q populations of an x-row side
 // by side (see k_pass3d), where a slice of it (a z-plane, a D2Q9 row) fits the
 // range of a buffer descriptor; else whole planes, as the state.  D3Q19 rows
-// start on 128-byte lines where that costs at most a sixteenth more.
-size_t second_pitch(const lb_params& p) {
-  const size_t row = (size_t)p.nx * elem_size(p.storage), up = (row + 127) & ~(size_t)127;
+// start on 128-byte lines where that costs at most a sixteenth more and the
+// device has room for it.
+size_t row_bytes(const lb_params& p) { return (size_t)p.nx * elem_size(p.storage); }
+size_t line_pitch(const lb_params& p) {
+  const size_t row = row_bytes(p), up = (row + 127) & ~(size_t)127;
   return p.lattice == LB_D3Q19 && (up - row) * 16 <= row ? up : row;
 }
-bool second_rows(const lb_params& p) {
+bool second_rows(const lb_params& p, size_t pitch) {
   const size_t rows = p.lattice == LB_D2Q9 ? 1 : (size_t)p.ny;
-  return (size_t)q_of(p.lattice) * rows * second_pitch(p) < (1ull << 32);
+  return (size_t)q_of(p.lattice) * rows * pitch < (1ull << 32);
 }
-size_t second_bytes(const lb_params& p) {
+size_t second_bytes(const lb_params& p, size_t pitch) {
   const size_t q = (size_t)q_of(p.lattice);
-  return second_rows(p) ? q * second_pitch(p) * p.ny * p.nz : q * sites_of(p) * elem_size(p.storage);
+  return second_rows(p, pitch) ? q * pitch * p.ny * p.nz : q * sites_of(p) * elem_size(p.storage);
 }
 
 // The second buffer is allocated once, if the device has room for it beside a
 // margin of 1 GiB.
 int ensure_state_b(lb_ctx* c) {
   if (c->d_state_b) return LB_OK;
-  const size_t bytes = second_bytes(c->reps[0]);
+  const lb_params& p = c->reps[0];
   size_t free_b = 0, total_b = 0;
   HIP_TRY(hipMemGetInfo(&free_b, &total_b));
-  if (free_b < bytes + (1ull << 30))
-    return fail(LB_EUNSUPPORTED, "not enough free device memory for the fused schedule's second state buffer");
-  const hipError_t e = hipMalloc(&c->d_state_b, bytes);
-  if (e != hipSuccess) {
+  hipError_t e = hipSuccess;
+  for (const size_t pitch : {line_pitch(p), row_bytes(p)}) {
+    const size_t bytes = second_bytes(p, pitch);
+    if (free_b < bytes + (1ull << 30)) continue;
+    e = hipMalloc(&c->d_state_b, bytes);
+    if (e == hipSuccess) {
+      c->pitch_b = pitch;
+      return LB_OK;
+    }
     c->d_state_b = nullptr;
     (void)hipGetLastError();
-    return fail(LB_EUNSUPPORTED, std::string("second state buffer of the fused schedule: ") + hipGetErrorString(e));
   }
-  return LB_OK;
+  if (e == hipSuccess)
+    return fail(LB_EUNSUPPORTED, "not enough free device memory for the fused schedule's second state buffer");
+  return fail(LB_EUNSUPPORTED, std::string("second state buffer of the fused schedule: ") + hipGetErrorString(e));
 }
 
 void release_state_b(lb_ctx* c) {
@@ -816,8 +825,8 @@ lb_ctx::PassArgs pass_args(const lb_ctx* c, const Clock& clock, const std::vecto
   const PassSide A{L.base, L.plane * elem_size(c->storage), slice, row, slice};
   PassSide B = A;
   B.base = (uint64_t)(uintptr_t)(c->uses_state_b() ? c->d_state_b : c->d_small_b);
-  if (second_rows(c->reps[0])) {
-    const uint32_t pitch = (uint32_t)second_pitch(c->reps[0]), q = (uint32_t)q_of(c->lattice);
+  if (!c->blocks && second_rows(c->reps[0], c->pitch_b)) {
+    const uint32_t pitch = (uint32_t)c->pitch_b, q = (uint32_t)q_of(c->lattice);
     B.plane = pitch;
     B.row = q * pitch;
     B.slice = B.span = c->lattice == LB_D2Q9 ? B.row : B.row * L.ny;
