@@ -179,13 +179,13 @@ def _stream_ptr(device, stream):
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
-def _is_current(stream, device):
-    """Whether stream is the caller's current stream of device.  Streams of two
-    devices may have one handle (the default streams do), so both count."""
+def _is_current(stream, index):
+    """Whether stream is the caller's current stream of the device of that
+    index.  Streams of two devices may have one handle (the default streams
+    do), so both count."""
     if _raw_stream is None:
-        return stream == torch.cuda.current_stream(device)
-    index = device.index if device.index is not None else torch.cuda.current_device()
-    return stream.device_index == index and stream.cuda_stream == _raw_stream(index)
+        return stream == torch.cuda.current_stream(index)
+    return stream.cuda_stream == _raw_stream(index) and stream.device_index == index
 
 
 def _adopt(t, device, lat_stream):
@@ -224,7 +224,7 @@ class _Gathers:
         caller's current stream may use at once."""
         lat_stream = self.stream if isinstance(self, Lattice) else self._ens.stream
         out = torch.empty((rows, *self._dims()), dtype=torch.float32, device=self.device)
-        other = not _is_current(lat_stream, self.device)
+        other = not _is_current(lat_stream, out.get_device())
         if other:
             _adopt(out, self.device, lat_stream)
         rc = fn(self._ctx, _aligned(out))
