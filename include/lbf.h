@@ -168,11 +168,10 @@ int lb_step(lb_ctx* ctx, int64_t nsteps);
  * the result is an exact permutation of the state.  The step count advances
  * as with lb_step, keeping the parity-resolved layout consistent (later
  * collisions draw the noise of the advanced counter).  On a batch every
- * replica moves.  Each step is one launch over the tiles of the current
- * schedule (one per replica group), with the memory accesses and cache
- * policy of the step kernel it replaces, so its duration is the
- * data-movement floor of that step.  Steps are launched one by one, never
- * from a graph replay. */
+ * replica moves.  The launches are those of lb_step, of one step or, where it
+ * takes them, of several, with the memory accesses and cache policy of the
+ * kernels they replace, so their duration is the data-movement floor of those
+ * steps.  They are launched one by one, never from a graph replay. */
 int lb_propagate(lb_ctx* ctx, int64_t nsteps);
 
 /* Parity-resolved gathers into caller-owned fp32 device buffers, each laid

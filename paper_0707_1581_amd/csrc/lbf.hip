@@ -385,7 +385,7 @@ struct lb_ctx {
   // d_meta (small ones) or d_state_b.
   char* d_small_b = nullptr;
   bool default_passes = false;
-  bool passes(bool prop) const { return sched.fused || (default_passes && !prop); }
+  bool passes() const { return sched.fused || default_passes; }
   bool uses_state_b() const { return sched.fused || (default_passes && !d_small_b); }
   struct PassArgs {
     const LatDesc* src;
@@ -690,7 +690,7 @@ int upload_schedule(lb_ctx* c) {
   HIP_TRY(hipMemcpy(c->d_tile_lats, tl.data(), sizeof(LatDesc) * nlat, hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(c->d_blk, blk.data(), sizeof(uint32_t) * (nlat + 1), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(c->d_blk_rows, blk_rows.data(), sizeof(uint32_t) * (nlat + 1), hipMemcpyHostToDevice));
-  if (c->passes(false)) {
+  if (c->passes()) {
     const int rc = plan_passes(c);
     if (rc) return rc;
   }
@@ -856,7 +856,7 @@ int launch_pass(lb_ctx* c, const Clock& clock, const std::vector<int>& ks, size_
 int build_graph(lb_ctx* c) {
   drop_graph(c);
   const int K = c->sched.graph_chunk;
-  const std::vector<int> ks = c->passes(false) ? pass_steps(c, K) : std::vector<int>();
+  const std::vector<int> ks = c->passes() ? pass_steps(c, K) : std::vector<int>();
   int covered = 0;
   for (int k : ks) covered += k;
   HIP_TRY(hipGraphCreate(&c->graph, 0));
@@ -908,7 +908,7 @@ int build_graph(lb_ctx* c) {
 int direct_steps(lb_ctx* c, int64_t m, bool prop = false) {
   int64_t s = 0;
   lb_ctx::Run run(c->d_t, c->t, m);
-  if (c->passes(prop) && !(c->t & 1)) {
+  if (c->passes() && !(c->t & 1)) {
     const std::vector<int> ks = pass_steps(c, m);
     for (size_t n = 0; n < ks.size(); ++n) {
       int rc = launch_pass(c, run.tick((uint64_t)s), ks, n, prop);
@@ -939,7 +939,7 @@ int advance(lb_ctx* c, int64_t n) {
   // the host stays ahead of them, and all n steps are divided among the passes
   // at once (20 steps of 16384^2 fp32: 34.9 ms, as a replay of 16 and 4 more
   // 38.0).
-  const bool long_passes = c->passes(false) && c->lats[0].plane * q_of(c->lattice) * elem_size(c->storage) >= 64000000;
+  const bool long_passes = c->passes() && c->lats[0].plane * q_of(c->lattice) * elem_size(c->storage) >= 64000000;
   const bool graphable = (uint64_t)K * c->groups.size() <= (1u << 16) && !long_passes;
   if (n >= K && graphable) {
     if (!c->graph_exec) {
@@ -1286,8 +1286,8 @@ int lb_propagate(lb_ctx* ctx, int64_t nsteps) {
   if (nsteps < 0) return fail(LB_EINVAL, "nsteps must be >= 0");
   if (nsteps == 0) return LB_OK;
   HIP_TRY(hipSetDevice(ctx->device));
-  // the same launches as lb_step's direct path (fused passes under the fused
-  // schedule), with the propagation-only kernels
+  // the same launches as lb_step's direct path (passes of several steps where
+  // it takes them), with the propagation-only kernels
   if (ctx->t & 1) {
     int rc = direct_steps(ctx, 1, true);
     if (rc) return rc;
