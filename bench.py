@@ -107,8 +107,8 @@ def launch_duration(lat, reps=10):
     """Mean duration (ms) of one launch of the run's step kernel, from HIP
     events on the lattice's stream around direct (never graph-replayed)
     calls: under the fused schedule lb_step(4) from even t is two fused
-    launches, otherwise lb_step(2) is one even and one odd AA launch; each
-    call also runs the 1-thread step-counter advance (a few microseconds)."""
+    launches (the first and the last of a chain), otherwise lb_step(2) is one
+    even and one odd AA launch."""
     import torch
     fused = lat.schedule()["fused"] == 1
     n = 4 if fused else 2
