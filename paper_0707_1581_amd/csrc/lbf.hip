@@ -425,14 +425,37 @@ void drop_graph(lb_ctx* c) {
 // idle costs a large part of a pass (256 planes 2651; 256^3: 43 planes, two
 // rounds nearly full, 308, 64 planes 403; 160^3: 27 planes 96, 20 planes 128).
 // The result does not depend on it.
+uint64_t chunk_cost(uint64_t across, uint32_t extent, uint32_t slots, uint32_t z) {
+  const uint64_t tiles = across * ((extent + z - 1u) / z);
+  return (tiles + slots - 1u) / slots * (uint64_t)(z + 3u);
+}
 uint32_t fused_chunk(uint64_t across, uint32_t extent, uint32_t slots) {
   constexpr uint32_t LONG = 128;
-  auto tiles = [&](uint32_t z) { return across * ((extent + z - 1u) / z); };
-  auto cost = [&](uint32_t z) { return ((tiles(z) + slots - 1u) / slots) * (uint64_t)(z + 3u); };
   uint32_t best = LONG;
   for (uint32_t z = 8; z < LONG; ++z)
-    if (cost(z) < cost(best)) best = z;
+    if (chunk_cost(across, extent, slots, z) < chunk_cost(across, extent, slots, best)) best = z;
   return best;
+}
+
+// Rows of a tile of that pass.  Tiles split the rows of the box evenly; the
+// fewest of them, of up to 13 rows, have the least halo, but where they leave the
+// rounds ill filled, smaller ones are faster, whose workgroups have fewer waves.
+// They are taken where the estimate above, times the waves of a workgroup, is 5%
+// lower (16 steps, us, with 13 rows and with these: 64^3 fp32 446 and 246, 128^3
+// 739 and 682, 200 x 157 x 160 2285 and 1953, 192^3 2268 and 2046, 300^3 9487 and
+// 9270).
+uint32_t tile_rows(uint32_t ntx, uint32_t ny, uint32_t nz, uint32_t slots) {
+  uint32_t rows = 0;
+  double best = 0.0;
+  for (uint32_t most = P3_TY; most > 0; --most) {
+    const uint32_t nty = (ny + most - 1u) / most, ty = (ny + nty - 1u) / nty;
+    const uint64_t across = (uint64_t)ntx * nty;
+    const double cost = (double)chunk_cost(across, nz, slots, fused_chunk(across, nz, slots)) * (ty + 3u);
+    if (rows && cost >= best) continue;
+    best = rows ? cost : 0.95 * cost;
+    rows = ty;
+  }
+  return rows;
 }
 
 // Rows a strip of the D2Q9 pass walks, of `across` strips, `extent` rows and
@@ -609,7 +632,8 @@ int plan_passes(lb_ctx* c) {
     const bool wide = k == 2 && c->storage == LB_F32 && bytes > 140000000 && L.ny >= (bytes > 200000000 ? 5u : 2u);
     const bool sync = wide || bytes > 320000000;
     const uint32_t waves = !wide ? S2_WAVES : bytes > 200000000 ? S2_WIDE_WAVES : S2_WIDE_WAVES / 2;
-    const uint32_t nty = (L.ny + P3_TY - 1u) / P3_TY, ty = (L.ny + nty - 1u) / nty;  // D3Q19: tiles along y, their rows
+    const uint32_t ntx = (L.nx + P3_TX - 1u) / P3_TX;  // D3Q19
+    const uint32_t ty = tile_rows(ntx, L.ny, L.nz, (uint32_t)cus);
     p.threads = 64 * (int)(c->lattice == LB_D2Q9 ? waves : ty + 3u);
     int per_cu = 0;
     HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pass_ptr(c->lattice, c->storage, k, p.threads, true, true, true, false), p.threads, 0));
@@ -632,8 +656,8 @@ int plan_passes(lb_ctx* c) {
       if (k == 4 && g.len >= four) c->pass_max = 4;
     } else {
       PassGeom& g = p.tiles;
-      g.ntx = (L.nx + (uint32_t)P3_TX - 1u) / (uint32_t)P3_TX;
-      g.nty = nty;
+      g.ntx = ntx;
+      g.nty = (L.ny + ty - 1u) / ty;
       g.tx = P3_TX;
       g.ty = ty;
       g.len = fused_chunk((uint64_t)g.ntx * g.nty, L.nz, slots);

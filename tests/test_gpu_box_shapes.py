@@ -103,8 +103,30 @@ def test_tiles_of_few_rows_not_slower(dims):
                                   (67, 157, 4)])
 @pytest.mark.parametrize("storage", ["f32", "f16"])
 def test_tiles_of_few_rows_keep_the_bits(dims, storage):
-    """Workgroups of 4 to 16 waves; a last tile of fewer rows than the others."""
+    """Boxes of few tiles, and a last tile of fewer rows than the others."""
     _same_bits("d3q19", dims, storage, 1, (4, 7, 8))
+
+
+@pytest.mark.parametrize("dims", [(63, 3325, 10), (70, 3001, 10), (65, 157, 200), (4100, 27, 20), (130, 1300, 9),
+                                  (8190, 13, 9), (4097, 14, 19), (16385, 1, 40)])
+def test_rows_of_the_tiles_keep_the_bits(dims):
+    """Boxes that fill the device: tiles of 13, 12, 10, 9, 8, 7, 5 and 1 rows,
+    the last one of 10, 1, 7, 9, 4, 6, 4 and 1."""
+    _same_bits("d3q19", dims, "f32", 1, (4, 7, 8))
+
+
+@pytest.mark.parametrize("dims,aa", [((64, 64, 64), 3.0), ((200, 157, 160), 1.05)])
+def test_tiles_that_leave_the_device_ill_filled(dims, aa):
+    """64^3 took 446 us for 16 steps in tiles of 13 rows, 246 in smaller ones, AA
+    steps 112; 200 x 157 x 160 2285, 1953 and 2064.  The bounds lie between."""
+    lats = [_lat("d3q19", dims, "f32") for _ in range(2)]
+    ms = []
+    for lat, fused in zip(lats, (0, 1)):
+        lat.set_schedule(**dict(lat.schedule(), fused=fused))
+        ms.append(_ms(lat))
+        lat.close()
+    say(f"{dims}: passes {1e3 * ms[1]:.0f} us, AA {1e3 * ms[0]:.0f} us")
+    assert ms[1] <= aa * ms[0]
 
 
 @pytest.mark.parametrize("dims,fused", [((400, 300, 350), 1), ((200, 300, 300), 0)])
