@@ -1045,8 +1045,13 @@ int init_lattice(lb_ctx* c, int idx, int kind, const float* d_fields, int parity
 // 28.5; 64^3 fp32 11.6 against 7.5; 300^3 fp16 512 against 404).  Rows that fill
 // the row tiles of one lattice keep them: fp32 above 320 MB on the even step,
 // without XCD groups (512 x 512 x 300 2141 against 2181), 16 bits on the odd step
-// (256 x 256 x 24 fp16 23.0 against 24.3), with XCD groups on D3Q19 and on D2Q9
-// of up to 128 MB (1024^2 bf16 10.6 against 12.0, but 16384^2 10% slower).
+// (256 x 256 x 24 fp16 23.0 against 24.3), with XCD groups but for D2Q9 above 320
+// MB (16384^2 bf16 10% slower).
+// 16-bit D2Q9 state that the XCDs' L2s do not hold (30 MB) and the Infinity Cache
+// does takes flat tiles, without XCD groups on the even step (2048^2 bf16 30.0
+// against 27.9 us; 4032 x 2250 57.0 and 57.0; ensembles of 27, 39 and 60 replicas
+// 536, 775 and 1168 against 515, 745 and 1114 for 32 steps; eight replicas, 10 MB,
+// 238 against 290).
 // A lattice whose planes are not whole 128-byte lines caches every access: a
 // tile ends inside lines of most planes, and streaming the parts costs far more
 // than caching them (441 x 318 x 225 fp16 654 against 515 us, fp32 1085 against
@@ -1068,11 +1073,14 @@ AaShape aa_shape(const lb_params* reps, size_t nrep) {
   const bool one = nrep == 1, f32 = reps[0].storage == LB_F32, wide = one && is_wide(reps[0]);
   const bool large = one && bytes > 320000000ull;
   const int block = sites <= 16384 ? 64 : sites <= 65536 ? 128 : 256;
+  const bool d2_16 = reps[0].lattice == LB_D2Q9 && !f32;
   AaShape s{block, {8, 8}, {0, 0}, false};
-  if (one && reps[0].nx % 256 == 0 && (large || !f32)) {
+  if (d2_16 && !large && bytes > 30000000ull) {
+    s.remap[0] = 0;
+  } else if (one && reps[0].nx % 256 == 0 && (large || !f32)) {
     s.block = 256;
     if (!wide) s.tiling[f32 ? 0 : 1] = 1;
-    if (f32 || (reps[0].lattice == LB_D2Q9 && bytes > 128000000ull)) s.remap[0] = s.remap[1] = 0;
+    if (f32 || (d2_16 && large)) s.remap[0] = s.remap[1] = 0;
   }
   s.cached = large && !wide && sites * elem_size(reps[0].storage) % 128 != 0;
   return s;

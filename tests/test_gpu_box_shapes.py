@@ -143,3 +143,33 @@ def test_noiseless_passes_from_the_measured_fill(dims, fused):
     assert torch.equal(lats[1].state, lats[2].state)
     for lat in lats:
         lat.close()
+
+
+# ---------------------------------------------------------------- AA launch shape of 16-bit D2Q9
+@pytest.mark.parametrize("dims,remap,tiling", [((1300, 1100, 1), [8, 8], [0, 0]), ((1024, 1024, 1), [8, 8], [0, 1]),
+                                               ((2048, 2048, 1), [0, 8], [0, 0]), ((4032, 2250, 1), [0, 8], [0, 0])])
+def test_shape_of_16_bit_d2q9_steps(dims, remap, tiling):
+    """On either side of the 30 MB that the L2s hold; the bits do not depend on it."""
+    lats = [_lat("d2q9", dims, "bf16") for _ in range(2)]
+    s = lats[0].schedule()
+    assert list(s["xcd_remap"]) == remap and list(s["tiling"]) == tiling, s
+    lats[1].set_schedule(block=128, xcd_remap=1, tiling=(1, 0))
+    for lat in lats:
+        lat.step(7)
+    assert torch.equal(lats[0].state, lats[1].state)
+    for lat in lats:
+        lat.close()
+
+
+@pytest.mark.parametrize("replicas,remap", [(3, [8, 8]), (9, [0, 8])])
+def test_shape_of_16_bit_d2q9_ensembles(replicas, remap):
+    reps = [dict(nx=701, ny=300, nz=1, kT=1e-4, gamma_shear=0.5, seed=k) for k in range(replicas)]
+    ens = lbf.Ensemble(reps, storage="f16", init="thermal", lattice="d2q9")  # 3.8 MB each
+    assert list(ens.schedule()["xcd_remap"]) == remap
+    ens.step(7)
+    for r in (0, replicas - 1):
+        lat = lbf.Lattice(**reps[r], storage="f16", init="thermal", lattice="d2q9")
+        lat.step(7)
+        assert torch.equal(ens.view(r).populations(), lat.populations())
+        lat.close()
+    ens.close()
