@@ -6,9 +6,9 @@
 // to another, so each population is read and written once per K steps.
 //
 // Work split.  A wave owns a strip of x-columns, one lane each, and walks a
-// chunk of rows along y with everything in registers; waves share nothing, so
-// there is no LDS and no barrier, and the waves of a SIMD cover each other's
-// loads.  The strip carries a halo of K - 1 columns on either side and the
+// chunk of rows along y with everything in registers; waves share no data, so
+// there is no LDS and, but for passes in step (below), no barrier, and the waves
+// of a SIMD cover each other's loads.  The strip carries a halo of K - 1 columns on either side and the
 // chunk one of K - 1 rows: step k is collided on K - k of them, which the
 // neighbouring waves collide too (58 of 64 lanes are interior at K = 4).  In
 // each phase the wave collides step 1 of the next row, step 2 of the row
@@ -31,7 +31,7 @@
 //
 // What bounds it: the issue of vector instructions for K = 3 and 4 (bf16 takes
 // as long as the collisions alone).  16384^2, 20 steps, per step: fp32 1.62 ms
-// (1.19 of 8 TB/s in algorithmic bytes) against 2.17 for the former two-step
+// (1.49 of 8 TB/s in algorithmic bytes) against 2.17 for the former two-step
 // pass (256-site segments with an LDS ring) and 3.36 for AA steps; bf16 1.55
 // against 1.86 and 1.76.
 //
