@@ -339,7 +339,7 @@ struct lb_ctx {
   };
   std::vector<Group> groups;
 
-  // graph of sched.graph_chunk steps starting at even t, plus the counter advance
+  // graph of sched.graph_chunk steps starting at even t
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
   struct StepArgs {
@@ -1806,7 +1806,7 @@ int autotune_timed(lb_ctx* ctx, int32_t steps, char* report, size_t report_len) 
     const int ngmb = ctx->lats.size() > 1 ? 7 : 1;
     for (int res = 0; res < (ctx->wide ? 1 : 2); ++res)
       for (int gi = 0; gi < ngmb; ++gi) vars.push_back({res, gmbs[gi], 0, 0.0});
-    // the fused two-step schedule, when its second buffer fits
+    // the fused schedule, when its second buffer fits
     if (rc == LB_OK && fused_eligible(ctx)) {
       const std::string keep = g_last_error;
       if (ensure_state_b(ctx) == LB_OK) vars.push_back({0, 0, 1, 0.0});
